@@ -32,6 +32,13 @@ __device__ __forceinline__ double t_sin<double>(double x) { return sin(x); }
 template <>
 __device__ __forceinline__ float t_sin<float>(float x) { return sinf(x); }
 
+template <typename T>
+__device__ __forceinline__ T t_sqrt(T x);
+template <>
+__device__ __forceinline__ double t_sqrt<double>(double x) { return sqrt(x); }
+template <>
+__device__ __forceinline__ float t_sqrt<float>(float x) { return sqrtf(x); }
+
 // Chebyshev-times-cutoff basis g[k] and dg/dr for k < K
 template <typename T>
 __device__ __forceinline__ void cheb_basis(int K, T rc, T r, T* g, T* dg) {

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <complex>
 #include <cstdio>
@@ -303,6 +304,178 @@ static bool real_cg(int l1, int l2, int L, std::vector<double>& out) {
 }
 
 // --------------------------------------------------------------------------
+// Tables of the FP64 rank kernels (k_ace_rank64.hip) from the folded
+// matrices.  *ok is false, and nothing else set, for models outside their
+// tiling: n_max > 8, more row tiles than the wavefronts' accumulators hold,
+// or an X_L that does not fit in LDS; those keep k_ace_fp64.
+using ChanMap = std::map<std::tuple<int, int, int>, int>;
+using CoefMap = std::map<std::pair<int, int>, std::pair<double, double>>;
+
+static ap_status fold_rank64(Ctx* ctx, const ChanMap& chan, const std::vector<CoefMap>& Cm,
+                             bool* ok) {
+  const AceDev& a = ctx->ace;
+  Rank64Dev& x = ctx->r64;
+  *ok = false;
+  const int lp1 = a.l_max + 1, nidx = a.n_max * lp1, nlm = a.nlm;
+  if (a.n_max > kRank64MaxN) return AP_OK;
+  constexpr int kMem = 64 / kT64;
+  x.n_max = a.n_max;
+  x.l_max = a.l_max;
+  x.nA = a.nA;
+  x.apad = a.nA | 1;
+  std::vector<int4> mem, units, jobs;
+  std::vector<int32_t> rowtab((size_t)(a.L_max + 1) * nidx * nidx, -1), kidx, job_ptr;
+  std::vector<double> coef;
+  std::vector<std::vector<std::vector<int>>> steps(a.L_max + 1);  // [L][unit]: its 4-column steps
+  for (int L = 0; L <= a.L_max; ++L) {
+    Rank64L& P = ctx->r64_lv[L];
+    P = Rank64L{};
+    const int w = 2 * L + 1;
+    P.nrow = a.nrow[L];
+    P.nrow4 = (P.nrow + 3) / 4 * 4;
+    P.zrow = P.nrow4;
+    P.nch = a.nch[L];
+    P.arow = a.has_arow[L];
+    // row stride: 8, 16 or 24 mod 32 doubles puts the four rows one operand
+    // read touches on different banks
+    P.cstr = (kT64 * w + 7) / 8 * 8;
+    if (P.cstr % 32 == 0) P.cstr += 8;
+    std::map<std::pair<int, int>, std::vector<int4>> by_pat;
+    std::vector<char> diag(P.nrow, 0);
+    for (auto& kv : chan) {
+      if (std::get<0>(kv.first) != L) continue;
+      const int xa = std::get<1>(kv.first), xb = std::get<2>(kv.first);
+      const int na = xa / lp1, la = xa % lp1, nb = xb / lp1, lb = xb % lp1;
+      rowtab[((size_t)L * nidx + xa) * nidx + xb] = kv.second;
+      rowtab[((size_t)L * nidx + xb) * nidx + xa] = kv.second;
+      diag[kv.second] = xa == xb;
+      by_pat[{la, lb}].push_back(make_int4(kv.second, na * nlm + la * la, nb * nlm + lb * lb, la * 5 + lb));
+    }
+    P.grp0 = (int32_t)(mem.size() / kMem);
+    for (auto& kv : by_pat)
+      for (size_t q = 0; q < (kv.second.size() + kMem - 1) / kMem * kMem; ++q)
+        mem.push_back(q < kv.second.size()
+                          ? kv.second[q]
+                          : make_int4(-1, 0, 0, kv.first.first * 5 + kv.first.second));
+    P.ngrp = (int32_t)(mem.size() / kMem) - P.grp0;
+    // row tiles of both sets and their steps; the diagonal channels' rows are
+    // doubled (both factors of A_a A_a depend on A_a)
+    std::vector<double> D((size_t)2 * P.nrow * P.nrow, 0.0);
+    for (auto& kv : Cm[L]) {
+      const int r = kv.first.first, c = kv.first.second;
+      const double f = r < P.nch && diag[r] ? 2.0 : 1.0;
+      D[(size_t)r * P.nrow + c] = f * kv.second.first;
+      D[((size_t)P.nrow + r) * P.nrow + c] = f * kv.second.second;
+    }
+    struct Unit { int row, set, s0, ns; };
+    std::vector<Unit> us;
+    for (int p = 0; p < 2; ++p)
+      for (int row = 0; row < P.nrow; row += 16) {
+        Unit u{row, p, (int)kidx.size(), 0};
+        for (int k = 0; k < P.nrow4; k += 4) {
+          double v[64];
+          bool any = false;
+          for (int l = 0; l < 64; ++l) {
+            const int r = row + l % 16, c = k + l / 16;
+            v[l] = r < P.nrow && c < P.nrow ? D[((size_t)p * P.nrow + r) * P.nrow + c] : 0.0;
+            any = any || v[l] != 0.0;
+          }
+          if (!any) continue;
+          kidx.push_back(k * P.cstr);
+          coef.insert(coef.end(), v, v + 64);
+          ++u.ns;
+        }
+        for (; u.ns % 4; ++u.ns) {  // the kernel takes steps four at a time
+          kidx.push_back(0);
+          coef.insert(coef.end(), 64, 0.0);
+        }
+        us.push_back(u);
+      }
+    // largest unit first onto the least loaded wavefront with a free slot
+    // (as few units per wavefront as possible: they all hold accumulators)
+    const int umax = ((int)us.size() + kMixWaves - 1) / kMixWaves;
+    if (umax > kRank64U[L]) return AP_OK;
+    std::stable_sort(us.begin(), us.end(), [](const Unit& p, const Unit& q) { return p.ns > q.ns; });
+    std::vector<std::vector<Unit>> per(kMixWaves);
+    std::vector<int> load(kMixWaves, 0);
+    for (auto& u : us) {
+      int best = -1;
+      for (int wv = 0; wv < kMixWaves; ++wv)
+        if ((int)per[wv].size() < umax && (best < 0 || load[wv] < load[best])) best = wv;
+      per[best].push_back(u);
+      load[best] += u.ns + 2;
+    }
+    for (auto& p : per) P.nu = std::max(P.nu, (int32_t)p.size());
+    P.unit0 = (int32_t)units.size();
+    for (auto& p : per)
+      for (int u = 0; u < P.nu; ++u)
+        units.push_back(u < (int)p.size() ? make_int4(p[u].row, p[u].set, p[u].s0, p[u].ns)
+                                          : make_int4(-1, 0, 0, 0));
+  }
+  // adjoint jobs, the same for both sets
+  constexpr int kMaxSlots = 4;
+  x.slots = 1;
+  for (int L = 0; L <= a.L_max; ++L) {
+    const int w = 2 * L + 1;
+    struct Job { int lt, lp, k; double cost; };
+    std::vector<Job> js;
+    for (int lt = 0; lt <= a.l_max; ++lt)
+      for (int lp = 0; lp <= a.l_max; ++lp) {
+        if (!(std::abs(lt - lp) <= L && L <= lt + lp && ((lt + lp + L) & 1) == 0)) continue;
+        bool any = false;
+        for (int na = 0; na < a.n_max && !any; ++na)
+          for (int nb = 0; nb < a.n_max && !any; ++nb)
+            any = rowtab[((size_t)L * nidx + na * lp1 + lt) * nidx + nb * lp1 + lp] >= 0;
+        if (!any) continue;
+        const int w2 = 2 * lp + 1, nc = rank64_chunks(lp, L);
+        for (int k = 0; k < nc; ++k) {
+          const int mc = (k + 1) * w / nc - k * w / nc;
+          js.push_back({lt, lp, k, 0.5 * a.n_max * (w2 * mc + 2.0 * (w2 + mc) + 12) + 2.0 * w2 * mc + 60});
+        }
+      }
+    std::stable_sort(js.begin(), js.end(), [](const Job& p, const Job& q) { return p.cost > q.cost; });
+    std::vector<std::vector<int4>> per(kMixWaves);
+    std::vector<double> load(kMixWaves, 0.0);
+    std::vector<std::vector<int>> slot(kMixWaves, std::vector<int>(lp1, -1));
+    std::vector<int> used(lp1, 0);
+    for (auto& j : js) {
+      int best = -1;
+      for (int wv = 0; wv < kMixWaves; ++wv)
+        if ((slot[wv][j.lt] >= 0 || used[j.lt] < kMaxSlots) && (best < 0 || load[wv] < load[best])) best = wv;
+      const bool first = slot[best][j.lt] < 0;
+      if (first) slot[best][j.lt] = used[j.lt]++;
+      per[best].push_back(make_int4((j.lt * 5 + j.lp) * 4 + j.k, slot[best][j.lt], first ? 1 : 0, j.lt));
+      load[best] += j.cost;
+    }
+    for (auto& p : per) {
+      job_ptr.push_back((int32_t)jobs.size());
+      jobs.insert(jobs.end(), p.begin(), p.end());
+    }
+    job_ptr.push_back((int32_t)jobs.size());
+    for (int l = 0; l < lp1; ++l) {
+      ctx->r64_lv[L].nslots[l] = used[l];
+      x.slots = std::max(x.slots, used[l]);
+    }
+  }
+  for (int L = 0; L <= a.L_max; ++L) {
+    const Rank64L& P = ctx->r64_lv[L];
+    // operand reads of the padding columns run up to 48 doubles past a row
+    ctx->r64_lds[L] = 8 * ((size_t)kT64 * x.apad * (1 + x.slots) + (size_t)(P.zrow + 1) * P.cstr) +
+                      (size_t)P.ngrp * kMem * 16 + ((size_t)nidx * nidx * 2 + 15) / 16 * 16 + 512;
+    if (ctx->r64_lds[L] > 160 * 1024) return AP_OK;
+    ctx->r64_lv[L].small = L <= kRank64LSmall && P.nu <= kRank64USmall && ctx->r64_lds[L] <= 80 * 1024;
+  }
+  ap_status st;
+  if ((st = upload_owned(ctx, mem, &x.grp_mem)) || (st = upload_owned(ctx, rowtab, &x.rowtab)) ||
+      (st = upload_owned(ctx, units, &x.units)) || (st = upload_owned(ctx, kidx, &x.kidx)) ||
+      (st = upload_owned(ctx, coef, &x.coef)) || (st = upload_owned(ctx, job_ptr, &x.job_ptr)) ||
+      (st = upload_owned(ctx, jobs, &x.jobs)))
+    return st;
+  *ok = true;
+  return AP_OK;
+}
+
+// --------------------------------------------------------------------------
 static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
   const int nmax = m->n_max, lmax = m->l_max, K = m->K;
   if (lmax < 0 || lmax > kMaxL) return fail(ctx, AP_ERR_ARG, "ACE l_max must be in [0, 4]");
@@ -372,7 +545,19 @@ static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
   }
   a.L_max = Lmax;
   int nch[2 * kMaxL + 1] = {0};
-  for (auto& kv : chan) kv.second = nch[std::get<0>(kv.first)]++;
+  if (ctx->precision == AP_PREC_FP64) {
+    // rows in (n_b, n_a) order: functions couple (a, b) with (c, d) only for
+    // b <= c, so this order gathers the zeros of C_L into whole tiles
+    std::vector<std::pair<std::array<int, 5>, int*>> rows;
+    for (auto& kv : chan) {
+      const int x = std::get<1>(kv.first), y = std::get<2>(kv.first);
+      rows.push_back({{std::get<0>(kv.first), y / lp1, x / lp1, y, x}, &kv.second});
+    }
+    std::sort(rows.begin(), rows.end());
+    for (auto& r : rows) *r.second = nch[r.first[0]]++;
+  } else {
+    for (auto& kv : chan) kv.second = nch[std::get<0>(kv.first)]++;
+  }
   int max_xsize = 0;
   for (int L = 0; L <= Lmax; ++L) {
     a.nch[L] = nch[L];
@@ -495,6 +680,8 @@ static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
   }
   ctx->ace_lds = ace_lds_bytes(a, ctx->precision);
   if (ctx->precision == AP_PREC_FP64) {
+    if ((st = fold_rank64(ctx, chan, Cm, &ctx->rank64))) return st;
+    if (ctx->rank64) return AP_OK;
     if (ctx->ace_lds > 160 * 1024) return fail(ctx, AP_ERR_UNSUPPORTED, "ACE model too large for LDS");
     return AP_OK;
   }
@@ -1212,9 +1399,39 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
   }
   const int32_t stamp = ++ctx->halo_stamp;
   int32_t* halo = (int32_t*)ctx->ace_halo.p;
-  if (ctx->precision == AP_PREC_FP64) {
+  const BondArgs ba{pos, (const double4*)ctx->pos4.p, nl->nbr, nl->count, nl->capacity, (int32_t)N,
+                    lambda, ace_list, n_ace, e_atom, vir, (double*)ctx->e_ace_raw.p,
+                    (int32_t*)ctx->nbr_ace.p, halo, stamp, vir_acc};
+  if (ctx->precision == AP_PREC_FP64 && ctx->rank64) {
+    const int nA = ctx->ace.nA;
+    // the list's length is on the device, so the buffers are sized for every
+    // atom, but at most kRank64Items at a time (1.3 GB for nA = 200): the
+    // three phases run batch after batch
+    const int n_buf = (int)std::min<int64_t>(std::max<int64_t>(N, 1), kRank64Items);
+    if ((st = ensure(ctx, ctx->mix_A, 8 * (size_t)n_buf * nA)) ||
+        (st = ensure(ctx, ctx->mix_om, 16 * (size_t)n_buf * nA)) ||
+        (st = ensure(ctx, ctx->mix_phi, 16 * (size_t)n_buf)))
+      return st;
+    double* A = (double*)ctx->mix_A.p;
+    double* om = (double*)ctx->mix_om.p;
+    double* phi = (double*)ctx->mix_phi.p;
+    for (int64_t i0 = 0; i0 < N; i0 += n_buf) {
+      {
+        PhaseTimer timer(ctx, AP_PHASE_ACE_BOND, s);
+        AP_HIP(launch_ace_bonds64(*ctx, sv, ba, 0, (int)i0, n_buf, (double*)ctx->pair_g.p, A, om, phi, s));
+      }
+      {
+        PhaseTimer timer(ctx, AP_PHASE_ACE, s);
+        AP_HIP(launch_ace_rank64(*ctx, ace_list ? n_ace : nullptr, (int)N, (int)i0, n_buf, A, om, phi, s));
+      }
+      {
+        PhaseTimer timer(ctx, AP_PHASE_ACE_BOND, s);
+        AP_HIP(launch_ace_bonds64(*ctx, sv, ba, 2, (int)i0, n_buf, (double*)ctx->pair_g.p, A, om, phi, s));
+      }
+    }
+  } else if (ctx->precision == AP_PREC_FP64) {
     PhaseTimer timer(ctx, AP_PHASE_ACE, s);
-    // the FP64 kernel takes atoms from a work counter
+    // the one-workgroup-per-atom kernel takes atoms from a work counter
     AP_HIP(launch_ace_reset((int32_t*)ctx->ace_counter.p, s));
     AP_HIP(launch_ace(*ctx, sv, pos, (const double4*)ctx->pos4.p, nl->nbr, nl->count, nl->capacity,
                       (int32_t)N, lambda, ace_list, n_ace, (int32_t*)ctx->ace_row.p,
@@ -1232,12 +1449,9 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
         const hipError_t e = launch_ace_reset((int32_t*)ctx->ace_counter.p, s);
         if (e != hipSuccess) return e;
       }
-      return launch_ace_mixed(*ctx, sv, pos, (const double4*)ctx->pos4.p, nl->nbr, nl->count,
-                              nl->capacity, (int32_t)N, lambda, ace_list, n_ace,
-                              (int32_t*)ctx->ace_counter.p, (float*)ctx->pair_g.p, (float*)ctx->mix_A.p,
-                              (float*)ctx->mix_om.p, (float*)ctx->mix_phi.p, (float*)ctx->mix_bn.p, e_atom,
-                              vir, s, phase, mode, (double*)ctx->e_ace_raw.p, (int32_t*)ctx->nbr_ace.p,
-                              halo, stamp, vir_acc);
+      return launch_ace_mixed(*ctx, sv, ba, (int32_t*)ctx->ace_counter.p, (float*)ctx->pair_g.p,
+                              (float*)ctx->mix_A.p, (float*)ctx->mix_om.p, (float*)ctx->mix_phi.p,
+                              (float*)ctx->mix_bn.p, s, phase, mode);
     };
     {
       PhaseTimer timer(ctx, AP_PHASE_ACE_BOND, s);

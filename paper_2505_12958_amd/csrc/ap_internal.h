@@ -153,6 +153,45 @@ struct MixDev {
   int32_t big_off, big_bytes;  // LDS layout
 };
 
+// ---- FP64 rank kernels (k_ace_rank64.hip): C_L as 16 x 4 tiles for the FP64
+// MFMA, empty tiles left out
+constexpr int kT64 = 4;              // atoms per tile
+constexpr int kRank64Items = 262144; // ACE atoms whose A and adjoint are held at once
+constexpr int kRank64MaxN = 8;       // lanes per atom of the adjoint: n_max <= 8
+// doubles of the adjoint's partner sum a lane holds at once (two VGPRs each)
+constexpr int kRank64Lim = 27;
+// units (16 rows of one set) per wavefront and rank: what the complete basis of
+// n_max 8, l_max 4, nu 4 needs
+constexpr int kRank64U[2 * kMaxL + 1] = {3, 5, 6, 6, 5, 3, 3, 1, 1};
+// L <= 1 with at most 3 units per wavefront runs in 128 VGPRs without spills, so
+// two workgroups share a CU (20,518 atoms of the (6, 3, nu <= 3) model: L = 0
+// 122 -> 85 us, L = 1 190 -> 124 us); at L >= 2 the budget spills (L = 2 284 ->
+// 290 us, L = 3 292 -> 308 us)
+constexpr int kRank64USmall = 3, kRank64LSmall = 1;
+// parts the M of rank L are cut into for a partner of rank lp (at most 4)
+__host__ __device__ constexpr int rank64_chunks(int lp, int L) {
+  const int n = ((2 * lp + 1) * (2 * L + 1) + kRank64Lim - 1) / kRank64Lim;
+  return n > 4 ? 4 : n;
+}
+struct Rank64L {
+  int32_t nrow, nrow4, nch, arow;   // rows of X_L, padded to the 4-row steps, channel rows, has A rows
+  int32_t zrow, cstr;               // row of zeros (= nrow4), row stride in doubles
+  int32_t grp0, ngrp;               // channel groups (64 / kT64 members each)
+  int32_t unit0, nu;                // first unit, units per wavefront
+  int32_t small;                    // two workgroups per CU
+  int32_t nslots[kMaxL + 1];        // gradient slots per target l
+};
+struct Rank64Dev {
+  int32_t n_max, l_max, nA, apad, slots;
+  const int4* grp_mem;              // {row (-1: none), A offset of a, of b, la * 5 + lb}
+  const int32_t* rowtab;            // [L][a][p]: row of the coupled channel {a, p}, or -1
+  const int4* units;                // {first row (-1: none), set, first step, steps}
+  const int32_t* kidx;              // per step: LDS offset of its 4 rows of X
+  const double* coef;               // per step: 16 x 4 coefficients in lane order
+  const int32_t* job_ptr;           // [L][kMixWaves + 1]
+  const int4* jobs;                 // {(lt * 5 + lp) * 4 + part, slot, first of its slot, lt}
+};
+
 struct Buffer {
   void* p = nullptr;
   size_t bytes = 0;
@@ -182,6 +221,12 @@ struct Ctx {
   EamAnalyticDev ean{};
   AceDev ace{};
   MixDev mix{};
+  // FP64 path: tables of the rank kernels; rank64 is false for models outside
+  // their tiling, which run the one-workgroup-per-atom kernel
+  bool rank64 = false;
+  Rank64Dev r64{};
+  Rank64L r64_lv[2 * kMaxL + 1]{};
+  size_t r64_lds[2 * kMaxL + 1] = {0};
   std::vector<Buffer> owned;            // model tables
   SysCache sys;
   // scratch, grown on demand
@@ -327,22 +372,54 @@ hipError_t launch_ace(const Ctx& c, const SysView& sv, const double* pos, const 
                       int32_t* counter, void* pair_g, double* e_atom, double* vir_atom,
                       double* e_raw, int32_t* nbr_ace, int32_t* halo, int32_t stamp,
                       bool vir_acc, hipStream_t s);
+// arguments the bond kernels of both precisions share
+struct BondArgs {
+  const double* pos;
+  const double4* pos4;
+  const int32_t* nbr;
+  const int32_t* count;
+  int32_t cap, n_atoms;
+  const double* lambda;
+  const int32_t* ace_list;
+  const int32_t* n_ace;
+  double* e_atom;
+  double* vir_atom;
+  double* e_raw;
+  int32_t* nbr_ace;
+  int32_t* halo;
+  int32_t stamp;
+  bool vir_acc;
+};
+// the model as the bond kernels of one precision read it
+template <typename T>
+struct BondDev {
+  int32_t n_max, l_max, K, nA, apad;
+  double rc;
+  const T* W;              // [n_max][l_max+1][K]
+  const double* ynorm;
+};
 // phase 0: bond basis -> A (and the listed atoms' rows, atom-major, ->
 // nbr_ace; the listed atoms and their neighbours stamped in halo); 1:
 // coupling/contraction/adjoint -> om, phi; 2: embedding, bond gradients, virial
-hipError_t launch_ace_mixed(const Ctx& c, const SysView& sv, const double* pos, const double4* pos4,
-                            const int32_t* nbr,
-                            const int32_t* count, int32_t cap, int32_t n_atoms, const double* lambda,
-                            const int32_t* ace_list, const int32_t* n_ace, int32_t* counter,
+hipError_t launch_ace_mixed(const Ctx& c, const SysView& sv, const BondArgs& b, int32_t* counter,
                             float* pair_g, float* A_buf, float* om_buf, float* phi_buf,
-                            float* bn_buf, double* e_atom, double* vir_atom, hipStream_t s,
-                            int phase, int rank_mode, double* e_raw, int32_t* nbr_ace,
-                            int32_t* halo, int32_t stamp, bool vir_acc);
+                            float* bn_buf, hipStream_t s, int phase, int rank_mode);
+// FP64 path: phases 0 and 2, and phase 1, over the items item0 .. item0 + n_buf - 1
+// (A, om, phi hold n_buf items)
+hipError_t launch_ace_bonds64(const Ctx& c, const SysView& sv, const BondArgs& b, int phase, int item0,
+                              int n_buf, double* pair_g, double* A_buf, double* om_buf,
+                              double* phi_buf, hipStream_t s);
+hipError_t launch_ace_rank64(const Ctx& c, const int32_t* n_ace, int n_atoms, int item0, int n_buf,
+                             double* A_buf, double* om_buf, double* phi_buf, hipStream_t s);
 size_t ace_mixed_lds_bytes(const MixDev& m);
 // the rank kernel of coupled rank L (k_ace_rank.hip, one translation unit
 // per L); xo: the variant that keeps X_L in LDS for both coefficient sets
 template <int L>
 const void* rank_kernel(bool xo);
+// FP64 rank kernel of coupled rank L (k_ace_rank64.hip); small: the variant
+// for two workgroups per CU (L <= kRank64LSmall)
+template <int L>
+const void* rank64_kernel(bool small);
 // all coupled ranks in one persistent launch (k_ace_rank_fused.hip) for the
 // rank layout (bit L of xomask: X_L kept for both sets; lmax: largest rank),
 // or NULL when no instance exists for that layout; queue: tiles from the

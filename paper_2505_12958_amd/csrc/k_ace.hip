@@ -1,5 +1,10 @@
-// ACE part of the AP force, FP64 path, and the gather that turns per-bond
-// gradients into forces.
+// ACE part of the AP force, FP64 path of the models outside the FP64 rank
+// kernels' tiling (k_ace_rank64.hip: n_max <= 8 and the complete basis of
+// l_max 4, nu 4), and the gather that turns per-bond gradients into forces.
+// Where both apply the rank kernels are faster (2,499 atoms of the (8, 4,
+// nu <= 4) model 1.15 against 4.46 ms; 20,518 atoms of (6, 3, nu <= 3) 0.92
+// against 4.27 ms): here the bond phases keep one wavefront of four busy and
+// the contraction is bound by random-column LDS reads.
 //
 // Per ACE-active atom i (one workgroup, persistent loop over a global atom
 // counter):
@@ -261,7 +266,8 @@ size_t ace_lds_bytes(const AceDev& a, int precision) {
 }
 
 // Stamps the listed atoms and their neighbours (the atoms the force gather
-// visits) for the FP64 path; the mixed path stamps them in its basis pass.
+// visits) for k_ace_fp64; the bond kernels of the other paths stamp them in
+// their basis pass.
 // Stamping inside k_ace_fp64 slowed that kernel by 7 %, so it has a pass of
 // its own: one wavefront per listed atom, one lane per slot.
 __global__ void k_ace_stamp(int n, const int32_t* __restrict__ nbr, const int32_t* __restrict__ count,

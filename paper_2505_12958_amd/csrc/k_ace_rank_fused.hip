@@ -145,13 +145,12 @@ __global__ __launch_bounds__(kMThreads, 1) void k_ace_rank_fused(
   }
 }
 
-// Instances for the rank layouts of the two model shapes of the workloads:
-// (n_max 8, l_max 4, nu <= 4): L_max 8, X_L kept at L = 0, 1, 2, 6, 7, 8;
-// (n_max 6, l_max 3, nu <= 3): L_max 3, X_L kept at every L.
-// Other layouts run one kernel per rank.
+// Instance for the rank layout of the (n_max 6, l_max 3, nu <= 3) model: L_max
+// 3, X_L kept at every L.  Other layouts run one kernel per rank: an instance
+// for (8, 4, nu <= 4) needs the register budget of its largest rank for all
+// nine and spills; it took 285 us against 278 us for the nine launches on 893
+// ACE atoms (one tile per workgroup) and 2.80 against 2.18 ms on 20,000.
 const void* rank_kernel_fused(bool queue, uint32_t xomask, int lmax) {
-  if (xomask == 0x1c7u && lmax == 8)
-    return queue ? (const void*)k_ace_rank_fused<true, 0x1c7u, 8> : (const void*)k_ace_rank_fused<false, 0x1c7u, 8>;
   if (xomask == 0xfu && lmax == 3)
     return queue ? (const void*)k_ace_rank_fused<true, 0xfu, 3> : (const void*)k_ace_rank_fused<false, 0xfu, 3>;
   return nullptr;
