@@ -20,6 +20,7 @@
 // sit in the channel-channel block, nu=3 in the channel-A block, nu=2 and
 // nu=1 against the constant row, so one quadratic form per L gives phi.
 #include <algorithm>
+#include <type_traits>
 
 #include "ace_basis.h"
 #include "ap_internal.h"
@@ -336,21 +337,55 @@ hipError_t launch_ace(const Ctx& c, const SysView& sv, const double* pos, const 
   return hipGetLastError();
 }
 
+// Slot of atom k in the ascending row of c entries (atom-major copy), or -1.
+// Rows of up to 64 entries (VEC: 16-byte aligned) take two rounds of
+// independent loads, three pivots and then one quarter of the row, where a
+// binary search takes six dependent ones.
+template <bool VEC>
+__device__ __forceinline__ int row_slot(const int32_t* __restrict__ row, int c, int k) {
+  if (VEC && c <= 64) {
+    int q = 0;
+#pragma unroll
+    for (int p = 1; p < 4; ++p) q += 16 * p <= c && row[min(16 * p, c) - 1] < k;
+    const int base = 16 * q;
+    int4 v[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      v[p] = *reinterpret_cast<const int4*>(row + (base + 4 * p < c ? base + 4 * p : 0));
+    int r = -1;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int s = base + 4 * p;
+      if (s < c && v[p].x == k) r = s;
+      if (s + 1 < c && v[p].y == k) r = s + 1;
+      if (s + 2 < c && v[p].z == k) r = s + 2;
+      if (s + 3 < c && v[p].w == k) r = s + 3;
+    }
+    return r;
+  }
+  int lo = 0, hi = c - 1;
+  while (lo <= hi) {
+    const int mid = (lo + hi) >> 1;
+    const int v = row[mid];
+    if (v == k) return mid;
+    if (v < k) lo = mid + 1; else hi = mid - 1;
+  }
+  return -1;
+}
+
 // F_k = sum_s g(k, s) - sum_s g(j_s, r_s) over the slots s of k, j_s = nbr(k, s),
 // where g(i, s) is the gradient of the ACE energy of listed atom i with
 // respect to its bond s and r_s is the slot of k in the row of j_s: read from
-// the full reverse index when the list has one (REV), else found by binary
-// search of j_s's ascending row in the atom-major copy the ACE kernels wrote
-// (nbr_ace, one row of cap entries per listed atom, so a search stays within
-// a few cache lines); both give the same value.  kGatherLanes lanes per atom,
-// lane l taking the slots s = l (mod kGatherLanes); the lanes' partial sums are
-// combined by a fixed butterfly, so the result is the same in every run and
-// with or without the reverse index.  Atoms not stamped for this evaluation
-// (the ACE kernels stamp every listed atom and its neighbours) have no ACE
-// term: zero, or unchanged when accumulating.
-constexpr int kGatherLanes = 4;
-
-template <typename G, bool REV>
+// the full reverse index when the list has one (REV), else searched in j_s's
+// row of the atom-major copy the ACE kernels wrote (nbr_ace, one row of cap
+// entries per listed atom, so a search stays within a few cache lines); both
+// give the same value.  LN lanes per atom, lane l taking the slots
+// s = l (mod LN); the lanes' partial sums are combined by a fixed butterfly, so
+// the result is the same in every run and with or without the reverse index.
+// Atoms not stamped for this evaluation (the ACE kernels stamp every listed
+// atom and its neighbours) have no ACE term: zero, or unchanged when
+// accumulating.
+template <typename G, bool REV, bool VEC, int LN>
 __global__ __launch_bounds__(256) void k_ace_gather(int n, const int32_t* __restrict__ nbr,
                                                     const int32_t* __restrict__ count,
                                                     const int32_t* __restrict__ rev,
@@ -360,8 +395,8 @@ __global__ __launch_bounds__(256) void k_ace_gather(int n, const int32_t* __rest
                                                     const G* __restrict__ g,
                                                     double* __restrict__ force, int accumulate) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int k = (int)(t / kGatherLanes);
-  const int l = (int)(t % kGatherLanes);
+  const int k = (int)(t / LN);
+  const int l = (int)(t % LN);
   // whole groups leave together: the butterfly below reads only lanes of its group
   if (k >= n) return;
   if (halo[k] != stamp) {
@@ -371,7 +406,7 @@ __global__ __launch_bounds__(256) void k_ace_gather(int n, const int32_t* __rest
   const int rk = row[k];
   const int c = count[k];
   double fx = 0, fy = 0, fz = 0;
-  for (int s = l; s < c; s += kGatherLanes) {
+  for (int s = l; s < c; s += LN) {
     if (rk >= 0) {
       const G* o = g + ((int64_t)rk * cap + s) * 3;
       fx += (double)o[0]; fy += (double)o[1]; fz += (double)o[2];
@@ -379,19 +414,8 @@ __global__ __launch_bounds__(256) void k_ace_gather(int n, const int32_t* __rest
     const int j = nbr[(int64_t)s * n + k];
     const int rj = row[j];
     if (rj >= 0) {
-      int r = -1;
-      if constexpr (REV) {
-        r = rev[(int64_t)s * n + k];
-      } else {
-        const int32_t* rowj = nbr_ace + (int64_t)rj * cap;
-        int lo = 0, hi = count[j] - 1;
-        while (lo <= hi) {
-          const int mid = (lo + hi) >> 1;
-          const int v = rowj[mid];
-          if (v == k) { r = mid; break; }
-          if (v < k) lo = mid + 1; else hi = mid - 1;
-        }
-      }
+      const int r = REV ? rev[(int64_t)s * n + k]
+                        : row_slot<VEC>(nbr_ace + (int64_t)rj * cap, count[j], k);
       if (r >= 0) {
         const G* o = g + ((int64_t)rj * cap + r) * 3;
         fx -= (double)o[0]; fy -= (double)o[1]; fz -= (double)o[2];
@@ -399,10 +423,10 @@ __global__ __launch_bounds__(256) void k_ace_gather(int n, const int32_t* __rest
     }
   }
 #pragma unroll
-  for (int d = kGatherLanes / 2; d >= 1; d >>= 1) {
-    fx += __shfl_xor(fx, d, kGatherLanes);
-    fy += __shfl_xor(fy, d, kGatherLanes);
-    fz += __shfl_xor(fz, d, kGatherLanes);
+  for (int d = LN / 2; d >= 1; d >>= 1) {
+    fx += __shfl_xor(fx, d, LN);
+    fy += __shfl_xor(fy, d, LN);
+    fz += __shfl_xor(fz, d, LN);
   }
   if (l != 0) return;
   if (accumulate) {
@@ -412,27 +436,38 @@ __global__ __launch_bounds__(256) void k_ace_gather(int n, const int32_t* __rest
   }
 }
 
+// Up to kGatherWide atoms the lanes' chains of dependent loads set the time:
+// 32 lanes per atom and the two-round search (250 atoms 38 -> 8.7 us, 31k 48 ->
+// 21 us, 54k 119 -> 80 us, 108k 47 -> 22 us against 4 lanes and binary search).
+// Beyond, the loads themselves do: 8 lanes and the binary search, which reads
+// less (250k atoms 113 us, with 32 lanes 149 us, two-round search and 32 lanes
+// 142 us; 390k atoms, all listed, 725 us with 4 lanes, 568 us with 8).
+constexpr int kGatherWide = 131072;
+
 hipError_t launch_ace_gather(const Ctx& c, int32_t n_atoms, const int32_t* nbr, const int32_t* count,
                              const int32_t* rev, const int32_t* nbr_ace, int32_t cap,
                              const int32_t* ace_row, const int32_t* halo, int32_t stamp,
                              const void* pair_g, double* force, bool accumulate, hipStream_t s) {
   if (n_atoms == 0) return hipSuccess;
-  const int64_t threads = (int64_t)n_atoms * kGatherLanes;
-  const dim3 g((unsigned)((threads + 255) / 256)), b(256);
   const int acc = accumulate ? 1 : 0;
-  const bool fp64 = c.precision == AP_PREC_FP64;
-  if (fp64 && rev)
-    hipLaunchKernelGGL((k_ace_gather<double, true>), g, b, 0, s, n_atoms, nbr, count, rev, nbr_ace,
-                       cap, ace_row, halo, stamp, (const double*)pair_g, force, acc);
-  else if (fp64)
-    hipLaunchKernelGGL((k_ace_gather<double, false>), g, b, 0, s, n_atoms, nbr, count, rev, nbr_ace,
-                       cap, ace_row, halo, stamp, (const double*)pair_g, force, acc);
-  else if (rev)
-    hipLaunchKernelGGL((k_ace_gather<float, true>), g, b, 0, s, n_atoms, nbr, count, rev, nbr_ace,
-                       cap, ace_row, halo, stamp, (const float*)pair_g, force, acc);
-  else
-    hipLaunchKernelGGL((k_ace_gather<float, false>), g, b, 0, s, n_atoms, nbr, count, rev, nbr_ace,
-                       cap, ace_row, halo, stamp, (const float*)pair_g, force, acc);
+  auto go = [&](auto kern, int lanes, auto* g) {
+    const int64_t threads = (int64_t)n_atoms * lanes;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, n_atoms, nbr,
+                       count, rev, nbr_ace, cap, ace_row, halo, stamp, g, force, acc);
+  };
+  auto pick = [&](auto* g) {
+    using G = std::remove_const_t<std::remove_pointer_t<decltype(g)>>;
+    if (n_atoms <= kGatherWide) {
+      if (rev) go(k_ace_gather<G, true, false, 32>, 32, g);
+      else if (cap % 4 == 0) go(k_ace_gather<G, false, true, 32>, 32, g);
+      else go(k_ace_gather<G, false, false, 32>, 32, g);
+    } else {
+      if (rev) go(k_ace_gather<G, true, false, 8>, 8, g);
+      else go(k_ace_gather<G, false, false, 8>, 8, g);
+    }
+  };
+  if (c.precision == AP_PREC_FP64) pick((const double*)pair_g);
+  else pick((const float*)pair_g);
   return hipGetLastError();
 }
 
