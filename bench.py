@@ -268,7 +268,7 @@ def roofline_model(ctx, ap, wl, n_ace, n_bonds, n_bonds_ace, fp64):
     return ph
 
 
-TRAFFIC_SOURCES = ["paper_2505_12958_amd/csrc/ace_rank.h", "paper_2505_12958_amd/csrc/k_ace_rank.hip",
+TRAFFIC_SOURCES = ["paper_2505_12958_amd/csrc/ace_rank32.h", "paper_2505_12958_amd/csrc/k_ace_rank32.hip",
                    "paper_2505_12958_amd/csrc/ap_internal.h", "paper_2505_12958_amd/csrc/ap_api.hip"]
 COPY_BYTES = 256 * 1024 * 1024        # the probe's elementwise kernel reads and writes 256 MiB
 
@@ -310,12 +310,12 @@ def record_traffic(fetch_csv, write_csv, key_json, out):
         raise SystemExit("no elementwise calibration kernel in the counter file")
     f_scale = COPY_BYTES / (fetch[calib[0]] * 1024.0)
     w_scale = COPY_BYTES / (write[calib[0]] * 1024.0)
-    ranks = sorted(k for k in fetch if re.search(r"k_ace_rank<", k))
+    ranks = sorted(k for k in fetch if re.search(r"k_ace_rank32<", k))
     fb = sum(fetch[k] for k in ranks) * 1024.0 * f_scale
     wb = sum(write.get(k, 0.0) for k in ranks) * 1024.0 * w_scale
     with open(key_json) as f:
         key = json.load(f)
-    rec = {"kernel": "k_ace_rank<L>, one launch per coupled rank, one pass",
+    rec = {"kernel": "k_ace_rank32<L>, one launch per coupled rank, one pass",
            "kernels": ranks, "key": key, "kernel_sources": TRAFFIC_SOURCES,
            "sources_sha256": sources_sha256(TRAFFIC_SOURCES),
            "fetch_bytes": fb, "write_bytes": wb, "traffic_bytes": fb + wb,
@@ -459,15 +459,16 @@ def main():
         roof = {
             "bound": "alu", "achieved": a_valu, "peak": PEAK["fp32_valu"], "unit": "TFLOP/s",
             "frac": a_valu / PEAK["fp32_valu"], "traffic": recorded_traffic(prec, ap, key),
-            "kernel": "k_ace_rank<L>, L=0..8 (coupling and adjoint on the vector ALUs; "
+            "kernel": "k_ace_rank32<L>, L=0..8 (coupling and adjoint on the vector ALUs; "
                       "split-fp16 contraction on MFMA)",
             "kernel_avg_ms": t_rank * 1e3, "valu_flops_per_pass": f_valu,
             "mfma": {"achieved": a_mfma, "peak": PEAK["f16_mfma"], "unit": "TFLOP/s",
                      "frac": a_mfma / PEAK["f16_mfma"], "flops_per_pass": f_mfma,
                      "executed_flops_per_pass": ctx.info("ace.mfma_flops_atom") * n_ace},
             "t_roof_ms": t_roof_rank * 1e3, "t_roof_frac": t_roof_rank / t_rank,
-            "launch_mode": ["one kernel per coupled rank", "all ranks in one persistent launch",
-                            "all ranks in one persistent launch, device work counter"][
+            "launch_mode": ["one kernel per coupled rank, narrow variants where a rank has one",
+                            "one kernel per coupled rank, wide variants",
+                            "one kernel per coupled rank, wide variants"][
                 int(ctx.info("ace.rank_mode"))],
         }
     roof["step"] = {"t_roof_ms": t_roof_step * 1e3, "ms_per_step": dt / args.steps * 1e3,

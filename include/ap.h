@@ -433,8 +433,9 @@ ap_status ap_profile_read(ap_ctx* ctx, double* ms, int64_t* calls, int32_t n);
  *   "eam.flops_bond"     FLOPs per bond of the two EAM passes;
  *   "ace.mfma_tiles"     stored 16x32 coefficient tiles of the mixed path;
  *   "ace.mfma_flops_atom" executed MFMA FLOPs per ACE atom of the mixed path
- *                        (three split products over the dense tiles);
- *   "ace.rank_mode"      launch mode of the last mixed rank phase (-1: none).
+ *                        (three split products over the stored tiles);
+ *   "ace.rank_mode"      variant of the last mixed rank phase: 0 narrow, 1 or 2
+ *                        wide (-1: none).
  * Returns AP_ERR_ARG for an unknown key. */
 ap_status ap_info(const ap_ctx* ctx, const char* key, double* value);
 

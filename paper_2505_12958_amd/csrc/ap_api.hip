@@ -393,14 +393,14 @@ static ap_status fold_rank64(Ctx* ctx, const ChanMap& chan, const std::vector<Co
       }
     // largest unit first onto the least loaded wavefront with a free slot
     // (as few units per wavefront as possible: they all hold accumulators)
-    const int umax = ((int)us.size() + kMixWaves - 1) / kMixWaves;
+    const int umax = ((int)us.size() + kRank64Waves - 1) / kRank64Waves;
     if (umax > kRank64U[L]) return AP_OK;
     std::stable_sort(us.begin(), us.end(), [](const Unit& p, const Unit& q) { return p.ns > q.ns; });
-    std::vector<std::vector<Unit>> per(kMixWaves);
-    std::vector<int> load(kMixWaves, 0);
+    std::vector<std::vector<Unit>> per(kRank64Waves);
+    std::vector<int> load(kRank64Waves, 0);
     for (auto& u : us) {
       int best = -1;
-      for (int wv = 0; wv < kMixWaves; ++wv)
+      for (int wv = 0; wv < kRank64Waves; ++wv)
         if ((int)per[wv].size() < umax && (best < 0 || load[wv] < load[best])) best = wv;
       per[best].push_back(u);
       load[best] += u.ns + 2;
@@ -434,13 +434,13 @@ static ap_status fold_rank64(Ctx* ctx, const ChanMap& chan, const std::vector<Co
         }
       }
     std::stable_sort(js.begin(), js.end(), [](const Job& p, const Job& q) { return p.cost > q.cost; });
-    std::vector<std::vector<int4>> per(kMixWaves);
-    std::vector<double> load(kMixWaves, 0.0);
-    std::vector<std::vector<int>> slot(kMixWaves, std::vector<int>(lp1, -1));
+    std::vector<std::vector<int4>> per(kRank64Waves);
+    std::vector<double> load(kRank64Waves, 0.0);
+    std::vector<std::vector<int>> slot(kRank64Waves, std::vector<int>(lp1, -1));
     std::vector<int> used(lp1, 0);
     for (auto& j : js) {
       int best = -1;
-      for (int wv = 0; wv < kMixWaves; ++wv)
+      for (int wv = 0; wv < kRank64Waves; ++wv)
         if ((slot[wv][j.lt] >= 0 || used[j.lt] < kMaxSlots) && (best < 0 || load[wv] < load[best])) best = wv;
       const bool first = slot[best][j.lt] < 0;
       if (first) slot[best][j.lt] = used[j.lt]++;
@@ -472,6 +472,237 @@ static ap_status fold_rank64(Ctx* ctx, const ChanMap& chan, const std::vector<Co
       (st = upload_owned(ctx, jobs, &x.jobs)))
     return st;
   *ok = true;
+  return AP_OK;
+}
+
+// --------------------------------------------------------------------------
+// Tables of the mixed rank kernels (k_ace_rank32.hip) from the folded
+// matrices.  Models outside their tiling (n_max > 8, too many rows per rank)
+// are refused.
+static ap_status fold_rank32(Ctx* ctx, const ChanMap& chan, const std::vector<CoefMap>& Cm) {
+  const AceDev& a = ctx->ace;
+  Rank32Dev& x = ctx->r32;
+  const int lp1 = a.l_max + 1, nidx = a.n_max * lp1, nlm = a.nlm;
+  const char* outside = "ACE model outside the mixed kernels' tiling (n_max <= 8, rows per rank)";
+  if (a.n_max > 8) return fail(ctx, AP_ERR_UNSUPPORTED, outside);
+  x.n_max = a.n_max;
+  x.l_max = a.l_max;
+  x.nA = a.nA;
+  x.apad = a.nA | 1;
+  std::vector<int4> mem, units, jobs;
+  std::vector<int32_t> rowtab((size_t)(a.L_max + 1) * nidx * nidx, -1), kidx, job_ptr;
+  std::vector<uint4> ctile;
+  std::vector<float> rscale;
+  // fp16 round-to-nearest-even of a float and back
+  auto f16_bits = [](float f) -> uint16_t {
+    const _Float16 h = (_Float16)f;
+    uint16_t u;
+    memcpy(&u, &h, 2);
+    return u;
+  };
+  auto f16_val = [](uint16_t b) -> float {
+    _Float16 h;
+    memcpy(&h, &b, 2);
+    return (float)h;
+  };
+  auto align = [](size_t v) { return (v + 15) / 16 * 16; };
+  auto tables = [&](Rank32L& P, size_t at) {
+    P.mem_off = (int32_t)align(at + 4 * (size_t)2 * P.nrow16);
+    P.rows_off = P.mem_off + P.ngrp * kMT32 * 16;
+  };
+  auto tables_end = [&](const Rank32L& P) { return P.rows_off + (size_t)nidx * (nidx + lp1) * 2; };
+  // X (the operand reads of the last column tile's padding run past lo) or Z
+  auto big_bytes = [&](const Rank32L& P, int L) {
+    const int w = 2 * L + 1, ct = (kMT32 * w + 15) / 16;
+    const int kstr = P.small ? kRank32KstrSmall : kRank32Kstr[L];
+    return std::max((size_t)(kMT32 * w + ct * 16) * kstr * 2, (size_t)(P.zrow + 1) * rank32_zstr(L) * 4);
+  };
+  double steps = 0, mfma = 0;
+  for (int L = 0; L <= a.L_max; ++L) {
+    Rank32L P{};
+    const int w = 2 * L + 1, ct = (kMT32 * w + 15) / 16;
+    P.nrow = a.nrow[L];
+    P.nrow8 = (P.nrow + 7) / 8 * 8;
+    P.nrow16 = (P.nrow + 15) / 16 * 16;
+    P.zrow = P.nrow;
+    P.nch = a.nch[L];
+    P.arow = a.has_arow[L];
+    if (P.nrow8 > kRank32Kstr[L]) return fail(ctx, AP_ERR_UNSUPPORTED, outside);
+    const bool narrow = L <= kRank32LSmall && a.nA <= kRank32NaSmall && P.nrow8 <= kRank32KstrSmall &&
+                        P.nrow16 / 16 <= kRank32WavesSmall * kRank32USmall;
+    std::map<std::pair<int, int>, std::vector<int4>> by_pat;
+    std::vector<char> diag(P.nrow, 0);
+    for (auto& kv : chan) {
+      if (std::get<0>(kv.first) != L) continue;
+      const int xa = std::get<1>(kv.first), xb = std::get<2>(kv.first);
+      const int na = xa / lp1, la = xa % lp1, nb = xb / lp1, lb = xb % lp1;
+      rowtab[((size_t)L * nidx + xa) * nidx + xb] = kv.second;
+      rowtab[((size_t)L * nidx + xb) * nidx + xa] = kv.second;
+      diag[kv.second] = xa == xb;
+      by_pat[{la, lb}].push_back(make_int4(kv.second, na * nlm + la * la, nb * nlm + lb * lb, la * 5 + lb));
+    }
+    P.grp0 = (int32_t)(mem.size() / kMT32);
+    for (auto& kv : by_pat)
+      for (size_t q = 0; q < (kv.second.size() + 7) / 8 * 8; ++q)
+        mem.push_back(q < kv.second.size() ? kv.second[q]
+                                           : make_int4(-1, 0, 0, kv.first.first * 5 + kv.first.second));
+    P.ngrp = (int32_t)(mem.size() / kMT32) - P.grp0;
+    std::vector<double> D((size_t)2 * P.nrow * P.nrow, 0.0);
+    for (auto& kv : Cm[L]) {
+      D[(size_t)kv.first.first * P.nrow + kv.first.second] = kv.second.first;
+      D[((size_t)P.nrow + kv.first.first) * P.nrow + kv.first.second] = kv.second.second;
+    }
+    // each row of each set is scaled by 2^e so that its largest entry lies
+    // in [2^12, 2^13): the fp16 hi/lo pieces then keep 22 significant bits of
+    // every entry that matters and no product overflows; the kernel
+    // multiplies the row's results by 2^-e (exact), for the diagonal channels
+    // by 2^(1 - e) (both factors of A_a A_a depend on A_a)
+    P.rs0 = (int32_t)rscale.size();
+    std::vector<int> rexp(2 * P.nrow16, 0);
+    for (int p = 0; p < 2; ++p)
+      for (int r = 0; r < P.nrow16; ++r) {
+        double mx = 0.0;
+        if (r < P.nrow)
+          for (int k = 0; k < P.nrow; ++k) mx = std::max(mx, std::fabs(D[((size_t)p * P.nrow + r) * P.nrow + k]));
+        int ex = 0;
+        if (mx > 0.0) (void)std::frexp((double)(float)mx, &ex);
+        const int e = mx > 0.0 ? 13 - ex : 0;
+        rexp[p * P.nrow16 + r] = e;
+        rscale.push_back(std::ldexp(1.0f, (r < P.nch && diag[r] ? 1 : 0) - e));
+      }
+    struct Unit { int row, set, s0, ns; };
+    std::vector<Unit> row_tiles;
+    for (int row = 0; row < P.nrow; row += 16) {
+      // the 8-column chunks in which one of the 16 rows has an entry in either
+      // set, four to a step
+      std::vector<int> ks;
+      for (int k = 0; k < P.nrow; k += 8) {
+        bool any = false;
+        for (int r = row; r < std::min(row + 16, P.nrow); ++r)
+          for (int c = k; c < std::min(k + 8, P.nrow); ++c)
+            any = any || D[(size_t)r * P.nrow + c] != 0.0 || D[((size_t)P.nrow + r) * P.nrow + c] != 0.0;
+        if (any) ks.push_back(k);
+      }
+      const int s0 = (int)(kidx.size() / 4);
+      int ns = ((int)ks.size() + 3) / 4;
+      if (ns & 1) ++ns;  // the kernel takes up to two steps at a time
+      for (int s = 0; s < ns; ++s) {
+        const size_t at = ctile.size();
+        ctile.resize(at + 256);
+        for (int q = 0; q < 4; ++q) {
+          const int j = 4 * s + q, k0 = j < (int)ks.size() ? ks[j] : 0;
+          kidx.push_back(k0);
+          for (int p = 0; p < 2; ++p)
+            for (int i = 0; i < 16; ++i) {
+              uint16_t hi[8], lo[8];
+              for (int e = 0; e < 8; ++e) {
+                const int r = row + i, c = k0 + e;
+                double v = 0.0;
+                if (j < (int)ks.size() && r < P.nrow && c < P.nrow)
+                  v = std::ldexp(D[((size_t)p * P.nrow + r) * P.nrow + c], rexp[p * P.nrow16 + r]);
+                hi[e] = f16_bits((float)v);
+                lo[e] = f16_bits((float)(v - (double)f16_val(hi[e])));
+              }
+              memcpy(&ctile[at + 128 * p + 16 * q + i], hi, 16);
+              memcpy(&ctile[at + 128 * p + 64 + 16 * q + i], lo, 16);
+            }
+        }
+      }
+      steps += 2 * ns;
+      mfma += 2 * 3.0 * 2.0 * 16 * 16 * 32 * ct * ns / kMT32;
+      row_tiles.push_back(Unit{row, 0, s0, ns});
+    }
+    // units, adjoint jobs and LDS layout of the two variants
+    for (int v = 0; v < 2; ++v) {
+      if (v == 1 && !narrow) {
+        ctx->r32_lv[1][L] = ctx->r32_lv[0][L];
+        ctx->r32_lds[1][L] = ctx->r32_lds[0][L];
+        continue;
+      }
+      P.small = v == 0 && narrow;
+      for (int l = 0; l < lp1; ++l) P.nslots[l] = 0;
+      std::vector<Unit> us = row_tiles;
+      if (!P.small && rank32_sets(L) == 1)
+        for (auto& u : row_tiles) us.push_back(Unit{u.row, 1, u.s0, u.ns});
+      const int nw = P.small ? kRank32WavesSmall : rank32_waves(L);
+      const int umax = ((int)us.size() + nw - 1) / nw;
+      if (umax > (P.small ? kRank32USmall : kRank32U[L])) return fail(ctx, AP_ERR_UNSUPPORTED, outside);
+      // largest unit first onto the least loaded wavefront with a free slot
+      std::stable_sort(us.begin(), us.end(), [](const Unit& p, const Unit& q) { return p.ns > q.ns; });
+      std::vector<std::vector<Unit>> per(nw);
+      std::vector<int> load(nw, 0);
+      for (auto& u : us) {
+        int best = -1;
+        for (int wv = 0; wv < nw; ++wv)
+          if ((int)per[wv].size() < umax && (best < 0 || load[wv] < load[best])) best = wv;
+        per[best].push_back(u);
+        load[best] += u.ns + 1;
+      }
+      P.nu = umax;
+      P.unit0 = (int32_t)units.size();
+      for (auto& p : per)
+        for (int u = 0; u < P.nu; ++u)
+          units.push_back(u < (int)p.size() ? make_int4(p[u].row, p[u].set, p[u].s0, p[u].ns)
+                                            : make_int4(-1, 0, 0, 0));
+      // adjoint jobs (the same for both sets), largest first
+      struct Job { int lt, lp, k; double cost; };
+      std::vector<Job> js;
+      for (int lt = 0; lt <= a.l_max; ++lt)
+        for (int lp = 0; lp <= a.l_max; ++lp) {
+          if (!(std::abs(lt - lp) <= L && L <= lt + lp && ((lt + lp + L) & 1) == 0)) continue;
+          bool any = false;
+          for (int na = 0; na < a.n_max && !any; ++na)
+            for (int nb = 0; nb < a.n_max && !any; ++nb)
+              any = rowtab[((size_t)L * nidx + na * lp1 + lt) * nidx + nb * lp1 + lp] >= 0;
+          if (!any) continue;
+          const int w2 = 2 * lp + 1, nc = rank32_chunks(lp, L);
+          for (int k = 0; k < nc; ++k) {
+            const int mc = (k + 1) * w / nc - k * w / nc;
+            js.push_back({lt, lp, k, a.n_max * (w2 * mc + 1.0 * (w2 + mc) + 12) + 2.0 * w2 * mc + 60});
+          }
+        }
+      std::stable_sort(js.begin(), js.end(), [](const Job& p, const Job& q) { return p.cost > q.cost; });
+      std::vector<std::vector<int4>> pj(nw);
+      std::vector<double> jl(nw, 0.0);
+      std::vector<std::vector<int>> slot(nw, std::vector<int>(lp1, -1));
+      for (auto& j : js) {
+        int best = -1;
+        for (int wv = 0; wv < nw; ++wv)
+          if ((slot[wv][j.lt] >= 0 || P.nslots[j.lt] < kSlots32) && (best < 0 || jl[wv] < jl[best])) best = wv;
+        const bool first = slot[best][j.lt] < 0;
+        if (first) slot[best][j.lt] = P.nslots[j.lt]++;
+        pj[best].push_back(make_int4((j.lt * 5 + j.lp) * 8 + j.k, slot[best][j.lt], first ? 1 : 0, j.lt));
+        jl[best] += j.cost;
+      }
+      P.job0 = (int32_t)job_ptr.size();
+      for (auto& p : pj) {
+        job_ptr.push_back((int32_t)jobs.size());
+        jobs.insert(jobs.end(), p.begin(), p.end());
+      }
+      job_ptr.push_back((int32_t)jobs.size());
+      P.phi_wave = (int32_t)(std::min_element(jl.begin(), jl.end()) - jl.begin());
+      P.slots = 1;
+      for (int l = 0; l < lp1; ++l) P.slots = std::max(P.slots, P.nslots[l]);
+      // LDS: A, slots, scales, channel groups, channel rows (and one spare row), X / Z
+      P.sx_off = (int32_t)(4 * (size_t)kMT32 * x.apad * (1 + P.slots));
+      P.rs_off = P.sx_off + 4 * kMT32;
+      tables(P, P.rs_off);
+      P.big_off = (int32_t)align(tables_end(P));
+      ctx->r32_lv[v][L] = P;
+      ctx->r32_lds[v][L] = P.big_off + big_bytes(P, L);
+      if (ctx->r32_lds[v][L] > 160 * 1024)
+        return fail(ctx, AP_ERR_UNSUPPORTED, "ACE model too large for the mixed kernel's LDS");
+    }
+    ctx->rank_narrow = ctx->rank_narrow || narrow;
+  }
+  ap_status st;
+  if ((st = upload_owned(ctx, mem, &x.grp_mem)) || (st = upload_owned(ctx, rowtab, &x.rowtab)) ||
+      (st = upload_owned(ctx, units, &x.units)) || (st = upload_owned(ctx, kidx, &x.kidx)) ||
+      (st = upload_owned(ctx, ctile, &x.ctile)) || (st = upload_owned(ctx, rscale, &x.rscale)) ||
+      (st = upload_owned(ctx, job_ptr, &x.job_ptr)) || (st = upload_owned(ctx, jobs, &x.jobs)))
+    return st;
+  ctx->mix_tiles = steps;
+  ctx->mix_mfma_flops = mfma;
   return AP_OK;
 }
 
@@ -545,7 +776,7 @@ static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
   }
   a.L_max = Lmax;
   int nch[2 * kMaxL + 1] = {0};
-  if (ctx->precision == AP_PREC_FP64) {
+  {
     // rows in (n_b, n_a) order: functions couple (a, b) with (c, d) only for
     // b <= c, so this order gathers the zeros of C_L into whole tiles
     std::vector<std::pair<std::array<int, 5>, int*>> rows;
@@ -555,8 +786,6 @@ static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
     }
     std::sort(rows.begin(), rows.end());
     for (auto& r : rows) *r.second = nch[r.first[0]]++;
-  } else {
-    for (auto& kv : chan) kv.second = nch[std::get<0>(kv.first)]++;
   }
   int max_xsize = 0;
   for (int L = 0; L <= Lmax; ++L) {
@@ -686,353 +915,31 @@ static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
     return AP_OK;
   }
 
-  // ---- mixed path: dense split-fp16 tiles with power-of-two row scales, channel groups
+  // ---- mixed path
+  if ((st = fold_rank32(ctx, chan, Cm))) return st;
   MixDev& x = ctx->mix;
-  x.n_max = nmax; x.l_max = lmax; x.K = K; x.nlm = nlm; x.nA = nA; x.nnl = a.nnl;
+  x.n_max = nmax; x.l_max = lmax; x.K = K; x.nA = nA;
   x.apad = nA | 1;
   x.L_max = Lmax;
   x.rc = m->r_c;
   x.Wf = a.Wf;
   x.ynorm = a.ynorm;
-  double mfma_flops = 0;
-  std::vector<int32_t> pat_off(225, -1);
-
-  std::vector<int32_t> grp_pat, pat_hdr;
-  std::vector<int4> grp_mem;
-  std::vector<CgEnt> pat_ent;
-  std::vector<float> pat_coef;
-  auto rule = [](int m1, int m2, int M) {
-    return ((M < 0) == ((m1 < 0) != (m2 < 0))) &&
-           (std::abs(M) == std::abs(m1) + std::abs(m2) || std::abs(M) == std::abs(std::abs(m1) - std::abs(m2)));
-  };
-  std::vector<uint4> ctile;
-  std::map<std::tuple<int, int, int>, int> pat_id;
-  size_t big = (size_t)4 * 64 * (a.nnl + nlm) * 4;
-  std::vector<size_t> xbytes(Lmax + 1, 0), zbytes(Lmax + 1, 0);
-  // fp16 round-to-nearest-even of a float and back
-  auto f16_bits = [](float f) -> uint16_t {
-    const _Float16 h = (_Float16)f;
-    uint16_t u;
-    memcpy(&u, &h, 2);
-    return u;
-  };
-  auto f16_val = [](uint16_t b) -> float {
-    _Float16 h;
-    memcpy(&h, &b, 2);
-    return (float)h;
-  };
-  std::vector<float> rscale;
-  // coupling coefficients of every valid (la, lb, L), over the selection-rule
-  // superset in (m1, m2, M) order, addressed by key la*45 + lb*9 + L
-  for (int la = 0; la <= lmax; ++la)
-    for (int lb = 0; lb <= lmax; ++lb)
-      for (int L = std::abs(la - lb); L <= std::min(la + lb, Lmax); ++L) {
-        if ((la + lb + L) & 1) continue;
-        auto key = std::make_tuple(la, lb, L);
-        if (!cgcache.count(key)) {
-          std::vector<double> c;
-          if (!real_cg(la, lb, L, c)) return fail(ctx, AP_ERR_ARG, "complex coupling coefficient");
-          cgcache[key] = c;
-        }
-        const auto& C = cgcache[key];
-        const int w1 = 2 * la + 1, w2 = 2 * lb + 1, w = 2 * L + 1;
-        pat_off[la * 45 + lb * 9 + L] = (int32_t)pat_coef.size();
-        for (int p = 0; p < w1; ++p)
-          for (int q = 0; q < w2; ++q)
-            for (int M = 0; M < w; ++M) {
-              const double c = C[((size_t)p * w2 + q) * w + M];
-              if (rule(p - la, q - lb, M - L)) {
-                pat_coef.push_back((float)c);
-              } else if (c != 0.0) {
-                return fail(ctx, AP_ERR_ARG, "coupling coefficient outside the selection rule");
-              }
-            }
-      }
-  // channel rows by unordered pair, for the adjoint gather
-  const int nidx = nmax * lp1;
-  std::vector<int32_t> rowtab((size_t)(Lmax + 1) * nidx * nidx, -1);
-  for (auto& kv : chan) {
-    const int L = std::get<0>(kv.first), xa = std::get<1>(kv.first), xb = std::get<2>(kv.first);
-    rowtab[((size_t)L * nidx + xa) * nidx + xb] = kv.second;
-    rowtab[((size_t)L * nidx + xb) * nidx + xa] = kv.second;
-  }
-  for (int L = 0; L <= Lmax; ++L) {
-    MixL& P = x.lv[L];
-    const int w = 2 * L + 1;
-    P.nrow = a.nrow[L];
-    P.nrow16 = (P.nrow + 15) / 16 * 16;
-    P.nch = nch[L];
-    P.arow = a.has_arow[L];
-    const int kpad = (P.nrow + 31) / 32 * 32;
-    P.kt = kpad / 32;
-    // column stride of the operand in LDS: kpad/2 is a multiple of 16 dwords,
-    // so the stride is 4 or 20 dwords mod 32 banks (an odd multiple of 4) and
-    // the 16-byte operand reads of 8 consecutive columns hit distinct banks
-    P.kstr = kpad + 8;
-    P.ct = (8 * w + 15) / 16;
-    P.rt = 2 * P.nrow16 / 16;
-    P.zstr = 8 * w + 1;
-    if ((P.nrow16 / 16 + kMixWaves - 1) / kMixWaves > kMixRtw[L] || P.ct != L + 1 || nmax > 8)
-      return fail(ctx, AP_ERR_UNSUPPORTED, "ACE model outside the mixed kernels' tiling (n_max <= 8, rows per rank)");
-    xbytes[L] = ((size_t)P.ct * 16 * P.kstr * 2 * 2 + 15) / 16 * 16;
-    zbytes[L] = (size_t)P.nrow * P.zstr * 4;
-    big = std::max(big, xbytes[L]);
-    big = std::max(big, zbytes[L]);
-    // dense folded matrix of this L (both sets)
-    std::vector<double> D((size_t)P.nrow * P.nrow * 2, 0.0);
-    for (auto& kv : Cm[L]) {
-      D[((size_t)kv.first.first * P.nrow + kv.first.second) * 2] = kv.second.first;
-      D[((size_t)kv.first.first * P.nrow + kv.first.second) * 2 + 1] = kv.second.second;
-    }
-    P.bt0 = (int32_t)(ctile.size() / 128);
-    // each row of each set is scaled by 2^e so that its largest entry lies
-    // in [2^12, 2^13): the fp16 hi/lo pieces then keep 22 significant bits of
-    // every entry that matters and no product overflows; the kernel
-    // multiplies the row's results by 2^-e (exact)
-    P.rs0 = (int32_t)rscale.size();
-    std::vector<int> rexp(2 * P.nrow16, 0);
-    for (int p = 0; p < 2; ++p)
-      for (int rr = 0; rr < P.nrow16; ++rr) {
-        double mx = 0.0;
-        if (rr < P.nrow)
-          for (int k = 0; k < P.nrow; ++k) mx = std::max(mx, std::fabs(D[((size_t)rr * P.nrow + k) * 2 + p]));
-        int ex = 0;
-        if (mx > 0.0) (void)std::frexp((double)(float)mx, &ex);
-        rexp[p * P.nrow16 + rr] = mx > 0.0 ? 13 - ex : 0;
-        rscale.push_back(std::ldexp(1.0f, -rexp[p * P.nrow16 + rr]));
-      }
-    for (int rt = 0; rt < P.rt; ++rt) {
-      for (int kt = 0; kt < P.kt; ++kt) {
-        double v[16][32];
-        bool any = false;
-        for (int i = 0; i < 16; ++i)
-          for (int kk = 0; kk < 32; ++kk) {
-            const int r = rt * 16 + i, k = kt * 32 + kk;
-            const int p = r / P.nrow16, rr = r % P.nrow16;
-            double val = 0.0;
-            if (rr < P.nrow && k < P.nrow) val = D[((size_t)rr * P.nrow + k) * 2 + p];
-            v[i][kk] = std::ldexp(val, rexp[r]);
-            any = any || val != 0.0;
-          }
-        (void)any;  // all tiles are stored (the folded matrices are almost dense)
-        mfma_flops += 3.0 * 2.0 * 16 * 16 * 32 * P.ct / 8.0;  // per atom (tile of 8 atoms)
-        const int idx = (int)(ctile.size() / 128);
-        ctile.resize(ctile.size() + 128);
-        for (int lane = 0; lane < 64; ++lane) {
-          uint16_t hi[8], lo[8];
-          for (int j = 0; j < 8; ++j) {
-            const double val = v[lane % 16][8 * (lane / 16) + j];
-            hi[j] = f16_bits((float)val);
-            lo[j] = f16_bits((float)(val - (double)f16_val(hi[j])));
-          }
-          uint4 h4, l4;
-          memcpy(&h4, hi, 16);
-          memcpy(&l4, lo, 16);
-          ctile[(size_t)idx * 128 + lane] = h4;
-          ctile[(size_t)idx * 128 + 64 + lane] = l4;
-        }
-      }
-    }
-    // channel groups of equal (la, lb)
-    std::map<std::pair<int, int>, std::vector<int4>> by_pat;
-    for (auto& kv : chan) {
-      if (std::get<0>(kv.first) != L) continue;
-      const int xa = std::get<1>(kv.first), xb = std::get<2>(kv.first);
-      const int na = xa / lp1, la = xa % lp1, nb = xb / lp1, lb = xb % lp1;
-      by_pat[{la, lb}].push_back(make_int4(kv.second, na * nlm + la * la, nb * nlm + lb * lb, la * 5 + lb));
-    }
-    P.grp0 = (int32_t)grp_pat.size();
-    for (auto& kv : by_pat) {
-      const int la = kv.first.first, lb = kv.first.second;
-      auto key = std::make_tuple(la, lb, L);
-      if (!pat_id.count(key)) {
-        const auto& C = cgcache[key];
-        const int e0 = (int)pat_ent.size();
-        const int w1 = 2 * la + 1, w2 = 2 * lb + 1;
-        for (int M = 0; M < w; ++M)
-          for (int p = 0; p < w1; ++p)
-            for (int q = 0; q < w2; ++q) {
-              const double c = C[((size_t)p * w2 + q) * w + M];
-              if (c != 0.0) pat_ent.push_back(CgEnt{(int8_t)p, (int8_t)q, (int8_t)M, 0, (float)c});
-            }
-        (void)e0;
-        pat_id[key] = (int)pat_hdr.size() / 5;
-        pat_hdr.insert(pat_hdr.end(), {la, lb, L, la * 45 + lb * 9 + L, pat_off[la * 45 + lb * 9 + L]});
-      }
-      const int pid = pat_id[key];
-      const auto& mem = kv.second;
-      // members of a group are taken with stride n_groups from the (a, b)
-      // ordered list, so they rarely share a single index
-      const size_t ng = (mem.size() + 7) / 8;
-      for (size_t g = 0; g < ng; ++g) {
-        grp_pat.push_back(pid);
-        for (size_t q = 0; q < 8; ++q) {
-          const size_t src = g + q * ng;
-          grp_mem.push_back(src < mem.size() ? mem[src] : make_int4(-1, 0, 0, la * 5 + lb));
-        }
-      }
-    }
-    P.ngrp = (int32_t)grp_pat.size() - P.grp0;
-  }
-  // adjoint jobs per L: (target l, component part K of NP) - every job owns
-  // its gradient entries, so no two wavefronts write the same entry.  The
-  // part counts and the assignment to wavefronts balance an estimated cost
-  // (largest job first onto the least-loaded wavefront).
-  std::vector<int32_t> adj_ptr;
-  std::vector<int4> adj_units;
-  for (int L = 0; L <= Lmax; ++L) {
-    const int w = 2 * L + 1;
-    // cost of the components [i0, i1) of target l = lt
-    auto job_cost = [&](int lt, int i0, int i1) {
-      double c = 0;
-      for (int lp = 0; lp <= lmax; ++lp) {
-        if (!(std::abs(lt - lp) <= L && L <= lt + lp && ((lt + lp + L) & 1) == 0)) continue;
-        const auto& C = cgcache[std::make_tuple(lt, lp, L)];
-        const int w2 = 2 * lp + 1;
-        // the partner sum W[m2][M] over the entries some component uses,
-        // then one pass over the coupling coefficients
-        int nnz = 0, used = 0;
-        for (int q = 0; q < w2; ++q)
-          for (int M = 0; M < w; ++M) {
-            bool u = false;
-            for (int p1 = i0; p1 < i1; ++p1)
-              if (C[((size_t)p1 * w2 + q) * w + M] != 0.0) {
-                ++nnz;
-                u = true;
-              }
-            used += u;
-          }
-        c += nmax * (used + w + 2.0 * w2 + 8.0) + nnz;
-      }
-      if (lt == L) c += 3.0 * (i1 - i0) + 12.0;
-      return c;
-    };
-    std::vector<int> np(lmax + 1, 1);
-    std::vector<bool> live(lmax + 1, false);
-    for (int lt = 0; lt <= lmax; ++lt) {
-      bool any = lt == L;
-      for (int lp = 0; lp <= lmax && !any; ++lp)
-        if (std::abs(lt - lp) <= L && L <= lt + lp && ((lt + lp + L) & 1) == 0) any = true;
-      live[lt] = any;
-    }
-    struct Job { int lt, npart, k; double cost; };
-    auto schedule = [&](std::vector<std::vector<Job>>& per) {
-      std::vector<Job> jobs;
-      for (int lt = 0; lt <= lmax; ++lt) {
-        if (!live[lt]) continue;
-        const int nc = 2 * lt + 1;
-        for (int k = 0; k < np[lt]; ++k)
-          jobs.push_back(Job{lt, np[lt], k, job_cost(lt, k * nc / np[lt], (k + 1) * nc / np[lt])});
-      }
-      std::stable_sort(jobs.begin(), jobs.end(), [](const Job& a, const Job& b) { return a.cost > b.cost; });
-      per.assign(kMixWaves, {});
-      std::vector<double> load(kMixWaves, 0.0);
-      for (auto& jb : jobs) {
-        const int wv = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-        per[wv].push_back(jb);
-        load[wv] += jb.cost;
-      }
-      return *std::max_element(load.begin(), load.end());
-    };
-    std::vector<std::vector<Job>> per;
-    double best = schedule(per);
-    for (;;) {
-      // split further the target whose job sits on the most loaded wavefront
-      int wmax = 0;
-      double lmax_w = -1;
-      for (int wv = 0; wv < kMixWaves; ++wv) {
-        double l = 0;
-        for (auto& jb : per[wv]) l += jb.cost;
-        if (l > lmax_w) { lmax_w = l; wmax = wv; }
-      }
-      int cand = -1;
-      double cc = -1;
-      for (auto& jb : per[wmax])
-        if (np[jb.lt] < 3 && np[jb.lt] < 2 * jb.lt + 1 && jb.cost > cc) { cc = jb.cost; cand = jb.lt; }
-      if (cand < 0) break;
-      ++np[cand];
-      std::vector<std::vector<Job>> trial;
-      const double t = schedule(trial);
-      if (t < best) {
-        best = t;
-        per = trial;
-      } else {
-        --np[cand];
-        break;
-      }
-    }
-    for (int wv = 0; wv < kMixWaves; ++wv) {
-      adj_ptr.push_back((int32_t)adj_units.size());
-      for (auto& jb : per[wv]) adj_units.push_back(make_int4(jb.lt * 16 + jb.npart * 4 + jb.k, 0, 0, jb.lt));
-    }
-    adj_ptr.push_back((int32_t)adj_units.size());
-  }
-  // LDS head: A, omega of both sets, phi [8][2], per-atom norm bound [8], the
-  // rank's partial phi sums [2][4][8], and the level parameters of every rank
-  // (fused kernel)
-  x.tab_off = (int32_t)(((size_t)(3 * 8 * x.apad + 16 + 8 + 64) * 4 + 15) / 16 * 16 +
-                        (size_t)(2 * kMaxL + 1) * kLevelInts * 4);
-  // the channel row table is staged as int16 (rows < 2^15)
-  for (int L = 0; L <= Lmax; ++L)
-    if (x.lv[L].nrow >= 32768) return fail(ctx, AP_ERR_UNSUPPORTED, "too many coupled rows for one rank");
-  const size_t rows_bytes = ((size_t)nidx * nidx * 2 + 15) / 16 * 16;
-  size_t tab = rows_bytes;
-  // per rank: the channel rows, the coupling groups and the row scales of both sets
-  for (int L = 0; L <= Lmax; ++L)
-    tab = std::max(tab, rows_bytes + (size_t)x.lv[L].ngrp * 8 * 16 + (size_t)x.lv[L].nrow16 * 2 * 4);
-  x.big_off = (int32_t)((x.tab_off + tab + 15) / 16 * 16);
-  // room the kernels' own static LDS needs beside the dynamic allocation
-  constexpr size_t kLdsReserve = 256;
-  // ranks whose X_L and Z_L fit in LDS together keep X_L for both sets
-  for (int L = 0; L <= Lmax; ++L) {
-    MixL& P = x.lv[L];
-    // Z_L's row stride: 8w + 4 floats puts the rows r and r + 4 that one store
-    // instruction writes (the MFMA result layout) 16 banks apart; 8w + 1 only
-    // where that is what lets X_L and Z_L fit together
-    const int w = 2 * L + 1;
-    // beside Z_L, X_L holds only the tile's 8w columns (hi, then lo); the
-    // contraction's reads of the last column tile's padding run on into the
-    // next region, which must cover them
-    const size_t x_tight = ((size_t)8 * w * P.kstr * 2 * 2 + 15) / 16 * 16;
-    const size_t overread = (size_t)(P.ct * 16 - 8 * w) * P.kstr * 2;
-    auto fits = [&](int zstr) {
-      const size_t zb = (size_t)P.nrow * zstr * 4;
-      return zb >= overread && (size_t)x.big_off + x_tight + zb + kLdsReserve <= 160 * 1024;
-    };
-    P.zstr = fits(8 * w + 4) || !fits(8 * w + 1) ? 8 * w + 4 : 8 * w + 1;
-    zbytes[L] = (size_t)P.nrow * P.zstr * 4;
-    P.xonce = fits(P.zstr) ? 1 : 0;
-    P.zoff = P.xonce ? (int32_t)x_tight : 0;
-    big = std::max(big, P.xonce ? x_tight + zbytes[L] : std::max(xbytes[L], zbytes[L]));
-  }
-  x.big_bytes = (int32_t)big;
-  if (ace_mixed_lds_bytes(x) + kLdsReserve > 160 * 1024)
-    return fail(ctx, AP_ERR_UNSUPPORTED, "ACE model too large for the mixed kernel's LDS");
-  if ((st = upload_owned(ctx, ctile, &x.ctile)) || (st = upload_owned(ctx, rscale, &x.rscale)) ||
-      (st = upload_owned(ctx, grp_pat, &x.grp_pat)) || (st = upload_owned(ctx, grp_mem, &x.grp_mem)) ||
-      (st = upload_owned(ctx, pat_hdr, &x.pat_hdr)) || (st = upload_owned(ctx, pat_ent, &x.pat_ent)) ||
-      (st = upload_owned(ctx, pat_coef, &x.pat_coef)) || (st = upload_owned(ctx, pat_off, &x.pat_off)) ||
-      (st = upload_owned(ctx, rowtab, &x.rowtab)) || (st = upload_owned(ctx, adj_ptr, &x.adj_ptr)) ||
-      (st = upload_owned(ctx, adj_units, &x.adj_units)))
-    return st;
-  {
-    std::vector<MixL> lv(x.lv, x.lv + Lmax + 1);
-    if ((st = upload_owned(ctx, lv, &x.lv_d))) return st;
-  }
-  ctx->mix_tiles = (double)(ctile.size() / 128);
-  ctx->mix_mfma_flops = mfma_flops;
   return AP_OK;
 }
 
 // --------------------------------------------------------------------------
-// Launch-mode tuner of the mixed rank phase.  The three modes (one kernel per
-// coupled rank; all ranks in one persistent launch, tiles round-robin; the
-// same with a device work counter) are timed with HIP events on the first
-// call of a context for each bucket of the atom count (powers of two), on that
-// call's own inputs, and the fastest is kept.  AP_RANK_MODE=0/1/2 forces a
-// mode; AP_AUTOTUNE=0 turns the tuner off (mode 1); AP_AUTOTUNE_CACHE names a
-// JSON file {"<device>|<model shape>|b<bucket>": mode, ...} that is read when
-// a context is created and updated after each tuning.
+// Tuner of the mixed rank phase.  Ranks with few channels have two variants
+// (workgroups of 4 wavefronts, three or four to a CU, or of 8 or 12); mode 0
+// runs the narrow one where it exists, mode 1 (2 means the same) the wide one.
+// Both are timed with HIP events on the first call of a context for each
+// bucket of the atom count (powers of two), on that call's own inputs, and the
+// faster is kept: the wide one has the shorter way through a single tile (250
+// ACE atoms of the (6, 3, nu <= 3) model 50 against 66 us, 7,849 atoms 126
+// against 132 us), the narrow one the higher throughput (389,694 atoms 3.4
+// against 4.0 ms).  Models without such ranks have mode 0 only.
+// AP_RANK_MODE=0/1/2 forces a mode; AP_AUTOTUNE=0 turns the tuner off (mode 1);
+// AP_AUTOTUNE_CACHE names a JSON file {"<device>|<model shape>|b<bucket>": mode,
+// ...} that is read when a context is created and updated after each tuning.
 static int size_bucket(int64_t n) {
   int b = 0;
   while ((int64_t(1) << (b + 1)) <= std::max<int64_t>(n, 1)) ++b;
@@ -1084,7 +991,7 @@ static void setup_tuner(Ctx* ctx, const ap_ace_model* m) {
     if (v >= 0 && v < AP_RANK_N_MODES) ctx->rank_mode_forced = v;
   }
   if (const char* f = std::getenv("AP_AUTOTUNE"))
-    if (std::string(f) == "0" && ctx->rank_mode_forced < 0) ctx->rank_mode_forced = AP_RANK_FUSED;
+    if (std::string(f) == "0" && ctx->rank_mode_forced < 0) ctx->rank_mode_forced = AP_RANK_WIDE;
   if (const char* f = std::getenv("AP_AUTOTUNE_CACHE")) {
     ctx->tune_cache = f;
     const std::string pre = ctx->tune_key + "|b";
@@ -1445,12 +1352,7 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
         (st = ensure(ctx, ctx->mix_phi, 8 * rows)) || (st = ensure(ctx, ctx->mix_bn, 4 * rows)))
       return st;
     auto phase_run = [&](int phase, int mode) -> hipError_t {
-      if (phase == 1 && mode == AP_RANK_FUSED_QUEUE) {
-        const hipError_t e = launch_ace_reset((int32_t*)ctx->ace_counter.p, s);
-        if (e != hipSuccess) return e;
-      }
-      return launch_ace_mixed(*ctx, sv, ba, (int32_t*)ctx->ace_counter.p, (float*)ctx->pair_g.p,
-                              (float*)ctx->mix_A.p, (float*)ctx->mix_om.p, (float*)ctx->mix_phi.p,
+      return launch_ace_mixed(*ctx, sv, ba, (float*)ctx->pair_g.p, (float*)ctx->mix_A.p, (float*)ctx->mix_om.p, (float*)ctx->mix_phi.p,
                               (float*)ctx->mix_bn.p, s, phase, mode);
     };
     {
@@ -1458,8 +1360,7 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
       AP_HIP(phase_run(0, 0));
     }
     int mode = ctx->rank_mode_forced;
-    if (mode > AP_RANK_PER_L && !rank_kernel_fused(false, rank_xomask(ctx->mix), ctx->mix.L_max))
-      mode = AP_RANK_PER_L;
+    if (mode > AP_RANK_NARROW && !ctx->rank_narrow) mode = AP_RANK_NARROW;
     if (mode < 0) {
       const int bucket = size_bucket(N);
       auto it = ctx->rank_mode_tuned.find(bucket);
@@ -1468,8 +1369,8 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
       } else {
         // time every mode twice on these inputs (the first round warms up);
         // each run rewrites the phase's outputs completely
-        // (the fused modes exist for the rank layouts with an instance)
-        const int n_modes = rank_kernel_fused(false, rank_xomask(ctx->mix), ctx->mix.L_max) ? AP_RANK_N_MODES : 1;
+        // (small models have two)
+        const int n_modes = ctx->rank_narrow ? 2 : 1;
         hipEvent_t ev[2 * AP_RANK_N_MODES];
         for (auto& e : ev) AP_HIP(hipEventCreate(&e));
         for (int rep = 0; rep < 2; ++rep)

@@ -100,57 +100,18 @@ struct AceDev {
   int32_t max_xsize;        // max_L nrow*(2L+1)
 };
 
-// ---- mixed-precision ACE model: per-L tiling, dense split-fp16 tiles,
-// channel groups of equal (l_a, l_b) with their coupling entries
-struct CgEnt {
-  int8_t m1, m2, M, pad;
-  float c;
-};
+// wavefronts of a workgroup of the FP64 rank kernels
+constexpr int kRank64Waves = 8;
+// modes of the mixed rank phase: the narrow variant of the ranks that have one
+// (few channels), or the wide variant of every rank (2 is accepted as 1)
+enum { AP_RANK_NARROW = 0, AP_RANK_WIDE = 1, AP_RANK_WIDE_2 = 2, AP_RANK_N_MODES = 3 };
 
-// Work-group shape of the mixed rank kernels: kMixWaves wavefronts; each
-// owns at most kMixRtw[L] 16-row tiles of one coefficient set of C_L
-// (row tile rt = wave + kMixWaves * i).
-constexpr int kMixWaves = 8;
-// int32 slots per rank of the level parameters the fused rank kernel stages in
-// LDS (the 15 fields of MixL, padded)
-constexpr int kLevelInts = 16;
-constexpr int kMixRtw[2 * kMaxL + 1] = {2, 3, 3, 3, 3, 2, 2, 1, 1};
-// launch modes of the rank phase: one kernel per coupled rank; all ranks in
-// one persistent launch with tiles round-robin; the same with tiles from a
-// device work counter
-enum { AP_RANK_PER_L = 0, AP_RANK_FUSED = 1, AP_RANK_FUSED_QUEUE = 2, AP_RANK_N_MODES = 3 };
-
-struct MixL {
-  int32_t nrow, nrow16, nch, arow;  // rows of X_L, padded to 16, channel rows, has A rows
-  int32_t rt, ct, kt;               // row tiles (both sets), column tiles, k tiles
-  int32_t kstr, zstr;               // LDS strides of the operand (fp16) and of Z (floats)
-  int32_t grp0, ngrp;               // channel groups of this L
-  int32_t bt0;                      // first coefficient tile of this L; tile (rt, kt) is bt0 + rt * kt_n + kt
-  int32_t xonce;                    // X_L stays in LDS for both sets (Z stored beside it at zoff)
-  int32_t zoff;                     // byte offset of Z within the big LDS region when xonce
-  int32_t rs0;                      // first row scale of this L in MixDev::rscale (set p at rs0 + p * nrow16)
-};
-
+// the ACE model as the mixed path's bond kernels read it
 struct MixDev {
-  int32_t n_max, l_max, K, nlm, nA, apad, nnl, L_max;
+  int32_t n_max, l_max, K, nA, apad, L_max;
   double rc;
   const float* Wf;
   const double* ynorm;
-  MixL lv[2 * kMaxL + 1];   // host copy
-  const MixL* lv_d;         // device copy (indexed by L in the kernel)
-  const uint4* ctile;      // dense tiles: (2 * tile + split) * 64 + lane, 8 fp16 per lane
-  const float* rscale;     // per coefficient row: 2^-e, the inverse of the row's power-of-two scale
-  const int32_t* grp_pat;  // pattern of each group
-  const int4* grp_mem;     // 8 members per group: {row, A offset of a, A offset of b, la*5+lb}
-  const int32_t* pat_hdr;  // 5 ints per pattern: la, lb, L, switch key, first coefficient
-  const CgEnt* pat_ent;
-  const float* pat_coef;   // coefficients per pattern over the selection-rule superset
-  const int32_t* pat_off;  // first coefficient of pattern key la*45 + lb*9 + L (-1: invalid)
-  const int32_t* rowtab;   // [L][a][p]: row of the coupled channel {a, p} in X_L, or -1
-  const int32_t* adj_ptr;  // [L][kMixWaves + 1]: each wavefront's adjoint units
-  const int4* adj_units;   // {l_t * 16 + parts * 4 + part, 0, 0, l_t}
-  int32_t tab_off;             // LDS: staged channel tables of one L (rows, groups)
-  int32_t big_off, big_bytes;  // LDS layout
 };
 
 // ---- FP64 rank kernels (k_ace_rank64.hip): C_L as 16 x 4 tiles for the FP64
@@ -188,8 +149,63 @@ struct Rank64Dev {
   const int4* units;                // {first row (-1: none), set, first step, steps}
   const int32_t* kidx;              // per step: LDS offset of its 4 rows of X
   const double* coef;               // per step: 16 x 4 coefficients in lane order
-  const int32_t* job_ptr;           // [L][kMixWaves + 1]
+  const int32_t* job_ptr;           // [L][kRank64Waves + 1]
   const int4* jobs;                 // {(lt * 5 + lp) * 4 + part, slot, first of its slot, lt}
+};
+
+// ---- mixed rank kernels (k_ace_rank32.hip): C_L as 16-row steps of four
+// 8-column chunks in split fp16, empty chunks left out
+constexpr int kMT32 = 8;             // atoms per tile
+__host__ __device__ constexpr int rank32_zstr(int L) { return 8 * (2 * L + 1) + 4; }
+// wavefronts per workgroup: 16 (128 VGPRs each) or 12 (168) fill a CU, two
+// workgroups of 8 (128) share it where their LDS fits
+__host__ __device__ constexpr int rank32_waves(int L) { return L < 2 || L > 6 ? 8 : 12; }
+constexpr int kRank32WavesSmall = 4;
+// wavefronts per SIMD (512 / this VGPRs each) and workgroups per CU
+__host__ __device__ constexpr int rank32_occ(int L, int nw) { return nw == 8 || L == 0 ? 4 : 3; }
+__host__ __device__ constexpr int rank32_groups(int L, int nw) { return 4 * rank32_occ(L, nw) / nw; }
+// sets a unit (16 rows) holds: both, which then share the operand reads of X,
+// but where a rank has fewer row tiles than wavefronts
+__host__ __device__ constexpr int rank32_sets(int L) { return L == 0 || L >= 7 ? 1 : 2; }
+// units per wavefront and k stride of X (fp16): what the complete basis of
+// n_max 8, l_max 4, nu 4 needs; the stride is 8, 24, 40 or 56 mod 64, so the
+// 16-byte operand reads of 8 consecutive columns hit distinct banks
+constexpr int kRank32U[2 * kMaxL + 1] = {3, 3, 2, 2, 2, 1, 1, 1, 1};
+constexpr int kRank32Kstr[2 * kMaxL + 1] = {200, 264, 344, 328, 312, 200, 136, 72, 40};
+// the narrow variant of L = 0..3 for models with few channels: 4 wavefronts per
+// workgroup, so that three or four workgroups share a CU
+constexpr int kRank32USmall = 3, kRank32KstrSmall = 136, kRank32LSmall = 3, kRank32NaSmall = 128;
+constexpr int kSlots32 = 4;          // gradient slots of a target l, at most
+// parts the M of rank L are cut into for a partner of rank lp: floats of the
+// adjoint's partner sum a lane holds beside the accumulators of the other set
+__host__ __device__ constexpr int rank32_chunks(int lp, int L) {
+  constexpr int lims[2 * kMaxL + 1] = {27, 27, 45, 42, 36, 54, 45, 27, 27};
+  const int lim = lims[L];
+  const int n = ((2 * lp + 1) * (2 * L + 1) + lim - 1) / lim;
+  return n > 6 ? 6 : n;
+}
+struct Rank32L {
+  int32_t nrow, nrow8, nrow16, nch, arow;  // rows of X_L, padded to chunks and row tiles
+  int32_t zrow;                            // row of zeros of Z (= nrow)
+  int32_t grp0, ngrp;                      // channel groups (8 members each)
+  int32_t unit0, nu;                       // first unit, units per wavefront
+  int32_t job0, rs0;                       // first entry of job_ptr, of rscale
+  int32_t slots, nslots[kMaxL + 1];        // gradient slots: most, per target l
+  // LDS offsets: column scales, row scales, channel groups, channel rows, X / Z
+  int32_t sx_off, rs_off, mem_off, rows_off, big_off;
+  int32_t phi_wave;                        // wavefront that sums phi
+  int32_t small;                           // the narrow variant
+};
+struct Rank32Dev {
+  int32_t n_max, l_max, nA, apad;
+  const int4* grp_mem;                     // {row (-1: none), A offset of a, of b, la * 5 + lb}
+  const int32_t* rowtab;                   // [L][a][p]: row of the coupled channel {a, p}, or -1
+  const int4* units;                       // {first row (-1: none), set, first step, steps}
+  const int32_t* kidx;                     // per step: first row of each of its four chunks
+  const uint4* ctile;                      // per step and set: 64 lanes of hi, 64 of lo (8 fp16 each)
+  const float* rscale;                     // per set and row: inverse of the row's scale
+  const int32_t* job_ptr;
+  const int4* jobs;                        // {(lt * 5 + lp) * 8 + part, slot, first of its slot, lt}
 };
 
 struct Buffer {
@@ -221,6 +237,10 @@ struct Ctx {
   EamAnalyticDev ean{};
   AceDev ace{};
   MixDev mix{};
+  Rank32Dev r32{};
+  Rank32L r32_lv[2][2 * kMaxL + 1]{};   // [narrow, wide][L]
+  size_t r32_lds[2][2 * kMaxL + 1] = {{0}};
+  bool rank_narrow = false;             // some rank has a narrow variant
   // FP64 path: tables of the rank kernels; rank64 is false for models outside
   // their tiling, which run the one-workgroup-per-atom kernel
   bool rank64 = false;
@@ -401,8 +421,7 @@ struct BondDev {
 // phase 0: bond basis -> A (and the listed atoms' rows, atom-major, ->
 // nbr_ace; the listed atoms and their neighbours stamped in halo); 1:
 // coupling/contraction/adjoint -> om, phi; 2: embedding, bond gradients, virial
-hipError_t launch_ace_mixed(const Ctx& c, const SysView& sv, const BondArgs& b, int32_t* counter,
-                            float* pair_g, float* A_buf, float* om_buf, float* phi_buf,
+hipError_t launch_ace_mixed(const Ctx& c, const SysView& sv, const BondArgs& b, float* pair_g, float* A_buf, float* om_buf, float* phi_buf,
                             float* bn_buf, hipStream_t s, int phase, int rank_mode);
 // FP64 path: phases 0 and 2, and phase 1, over the items item0 .. item0 + n_buf - 1
 // (A, om, phi hold n_buf items)
@@ -411,21 +430,14 @@ hipError_t launch_ace_bonds64(const Ctx& c, const SysView& sv, const BondArgs& b
                               double* phi_buf, hipStream_t s);
 hipError_t launch_ace_rank64(const Ctx& c, const int32_t* n_ace, int n_atoms, int item0, int n_buf,
                              double* A_buf, double* om_buf, double* phi_buf, hipStream_t s);
-size_t ace_mixed_lds_bytes(const MixDev& m);
-// the rank kernel of coupled rank L (k_ace_rank.hip, one translation unit
-// per L); xo: the variant that keeps X_L in LDS for both coefficient sets
+// mixed rank kernel of coupled rank L (k_ace_rank32.hip); small: the narrow
+// variant
 template <int L>
-const void* rank_kernel(bool xo);
+const void* rank32_kernel(bool small);
 // FP64 rank kernel of coupled rank L (k_ace_rank64.hip); small: the variant
 // for two workgroups per CU (L <= kRank64LSmall)
 template <int L>
 const void* rank64_kernel(bool small);
-// all coupled ranks in one persistent launch (k_ace_rank_fused.hip) for the
-// rank layout (bit L of xomask: X_L kept for both sets; lmax: largest rank),
-// or NULL when no instance exists for that layout; queue: tiles from the
-// device work counter instead of round-robin
-const void* rank_kernel_fused(bool queue, uint32_t xomask, int lmax);
-uint32_t rank_xomask(const MixDev& m);
 hipError_t launch_ace_gather(const Ctx& c, int32_t n_atoms, const int32_t* nbr, const int32_t* count,
                              const int32_t* rev, const int32_t* nbr_ace, int32_t cap,
                              const int32_t* ace_row, const int32_t* halo, int32_t stamp,

@@ -12,12 +12,12 @@ OUT = os.path.join(PKG, "libap.so")
 OBJ = os.path.join(PKG, "_build")
 
 SOURCES = ["ap_api.hip", "k_nbr.hip", "k_misc.hip", "k_eam.hip", "k_ace.hip", "k_ace_mixed.hip",
-           "k_ace_rank_fused.hip", "k_switch.hip"]
+           "k_switch.hip"]
 # (source, object name, extra flags): the rank kernels are compiled once
 # per coupled rank L, in parallel
 UNITS = [(s, s.replace(".hip", ""), []) for s in SOURCES] + [
     (src, f"{src[:-len('.hip')]}_L{L}", [f"-DAP_RANK_L={L}"])
-    for src in ("k_ace_rank.hip", "k_ace_rank64.hip") for L in range(9)]
+    for src in ("k_ace_rank32.hip", "k_ace_rank64.hip") for L in range(9)]
 ARCH = os.environ.get("AP_OFFLOAD_ARCH", "gfx950")
 COMMON = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

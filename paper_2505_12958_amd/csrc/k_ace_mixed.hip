@@ -144,7 +144,7 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_basis(
 }
 
 // ---- kernel 3: embedding (FP64), bond gradients and virial, one wavefront per atom
-// om_in: the two sets interleaved (mixed) or n_buf * nA apart (FP64)
+// om_in: the two sets are n_buf * nA apart
 template <typename T, int NM, int LM, int KK>
 __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_grad(
     SysView sv, BondDev<T> m, const double* __restrict__ pos, const double4* __restrict__ pos4,
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_grad(
   if (local >= n_buf || item >= n_items) return;  // whole wavefront
   const int64_t plane = (int64_t)n_buf * m.nA;
   auto om_at = [&](int64_t o, int p) {
-    return (double)(sizeof(T) == 8 ? om_in[o + p * plane] : om_in[2 * o + p]);
+    return (double)om_in[o + p * plane];
   };
   const int a = ace_list ? ace_list[item] : item;
   const double lam = lambda ? lambda[a] : 1.0;
@@ -263,15 +263,6 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_grad(
   }
 }
 
-size_t ace_mixed_lds_bytes(const MixDev& m) { return m.big_off + m.big_bytes; }
-
-uint32_t rank_xomask(const MixDev& m) {
-  uint32_t x = 0;
-  for (int L = 0; L <= m.L_max; ++L)
-    if (m.lv[L].xonce) x |= 1u << L;
-  return x;
-}
-
 // kernels 1 and 3 of one precision over the items item0 .. item0 + n_buf - 1
 // (grids are sized for all of them; wavefronts past *n_ace leave at once)
 template <typename T>
@@ -352,14 +343,13 @@ hipError_t launch_ace_rank64(const Ctx& c, const int32_t* n_ace, int n_atoms, in
     const int per_cu = sm ? 2 : 1;
     void* args[] = {(void*)&c.r64, (void*)&P, (void*)&n_ace, (void*)&n_atoms, (void*)&item0,
                     (void*)&n_buf, (void*)&A_buf, (void*)&om_buf, (void*)&phi_buf};
-    e = hipLaunchKernel(fn, dim3(std::min(tiles, n_cu * per_cu)), dim3(64 * kMixWaves), args, lds, s);
+    e = hipLaunchKernel(fn, dim3(std::min(tiles, n_cu * per_cu)), dim3(64 * kRank64Waves), args, lds, s);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_ace_mixed(const Ctx& c, const SysView& sv, const BondArgs& b, int32_t* counter,
-                            float* pair_g, float* A_buf, float* om_buf, float* phi_buf,
+hipError_t launch_ace_mixed(const Ctx& c, const SysView& sv, const BondArgs& b, float* pair_g, float* A_buf, float* om_buf, float* phi_buf,
                             float* bn_buf, hipStream_t s, int phase, int rank_mode) {
   const MixDev& m = c.mix;
   const int n_atoms = b.n_atoms;
@@ -370,41 +360,34 @@ hipError_t launch_ace_mixed(const Ctx& c, const SysView& sv, const BondArgs& b, 
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  const size_t lds = ace_mixed_lds_bytes(m);
   const int32_t* na = b.ace_list ? b.n_ace : nullptr;
-  if (rank_mode != AP_RANK_PER_L) {
-    // one persistent launch over all coupled ranks; the work counter was
-    // reset on the stream before this phase
-    const void* fn = rank_kernel_fused(rank_mode == AP_RANK_FUSED_QUEUE, rank_xomask(m), m.L_max);
-    if (!fn) return hipErrorInvalidDeviceFunction;
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    void* args[] = {(void*)&m, (void*)&na, (void*)&n_atoms, (void*)&A_buf, (void*)&om_buf,
-                    (void*)&phi_buf, (void*)&bn_buf, (void*)&counter};
-    e = hipLaunchKernel(fn, dim3(n_cu), dim3(64 * kMixWaves), args, lds, s);
-    if (e != hipSuccess) return e;
-    return hipGetLastError();
-  }
+  const int tiles = (n_atoms + kMT32 - 1) / kMT32;
+  if (tiles == 0) return hipSuccess;
+  const int v = rank_mode == AP_RANK_NARROW ? 0 : 1;
   for (int L = 0; L <= m.L_max; ++L) {
+    const Rank32L& P = c.r32_lv[v][L];
+    if (P.nrow == 0) continue;
     const void* fn = nullptr;
-    // X_L kept for both sets when it fits beside Z_L (decided with the LDS layout)
-    const bool xo = m.lv[L].xonce != 0;
+    const bool sm = P.small != 0;
     switch (L) {
-      case 0: fn = rank_kernel<0>(xo); break;
-      case 1: fn = rank_kernel<1>(xo); break;
-      case 2: fn = rank_kernel<2>(xo); break;
-      case 3: fn = rank_kernel<3>(xo); break;
-      case 4: fn = rank_kernel<4>(xo); break;
-      case 5: fn = rank_kernel<5>(xo); break;
-      case 6: fn = rank_kernel<6>(xo); break;
-      case 7: fn = rank_kernel<7>(xo); break;
-      default: fn = rank_kernel<8>(xo); break;
+      case 0: fn = rank32_kernel<0>(sm); break;
+      case 1: fn = rank32_kernel<1>(sm); break;
+      case 2: fn = rank32_kernel<2>(sm); break;
+      case 3: fn = rank32_kernel<3>(sm); break;
+      case 4: fn = rank32_kernel<4>(sm); break;
+      case 5: fn = rank32_kernel<5>(sm); break;
+      case 6: fn = rank32_kernel<6>(sm); break;
+      case 7: fn = rank32_kernel<7>(sm); break;
+      default: fn = rank32_kernel<8>(sm); break;
     }
+    const int nw = sm ? kRank32WavesSmall : rank32_waves(L);
+    const size_t lds = c.r32_lds[v][L];
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    void* args[] = {(void*)&m, (void*)&na, (void*)&n_atoms, (void*)&A_buf, (void*)&om_buf,
-                    (void*)&phi_buf, (void*)&bn_buf};
-    e = hipLaunchKernel(fn, dim3(n_cu), dim3(64 * kMixWaves), args, lds, s);
+    const int per_cu = std::min<int>(rank32_groups(L, nw), 160 * 1024 / lds);
+    void* args[] = {(void*)&c.r32, (void*)&P, (void*)&na, (void*)&n_atoms, (void*)&A_buf,
+                    (void*)&om_buf, (void*)&phi_buf, (void*)&bn_buf};
+    e = hipLaunchKernel(fn, dim3(std::min(tiles, n_cu * per_cu)), dim3(64 * nw), args, lds, s);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();

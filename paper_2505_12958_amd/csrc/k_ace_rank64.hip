@@ -46,7 +46,7 @@ namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads64 = 64 * kMixWaves;
+constexpr int kThreads64 = 64 * kRank64Waves;
 
 // Read-only tables through the constant address space: wavefront-uniform
 // indices become scalar loads (the kernel never writes them).
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kThreads64, SMALL ? 4 : 2) void k_ace_rank64(
     gz[r] = P.arow && l == L ? (P.nch + nn) * P.cstr + t * w + lm - L * L : -1;
   }
   cptr<int32_t> units = as_const(reinterpret_cast<const int32_t*>(m.units)) + 4 * (P.unit0 + wave * P.nu);
-  cptr<int32_t> jptr = as_const(m.job_ptr) + L * (kMixWaves + 1);
+  cptr<int32_t> jptr = as_const(m.job_ptr) + L * (kRank64Waves + 1);
   cptr<int32_t> jobs = as_const(reinterpret_cast<const int32_t*>(m.jobs));
   cptr<int32_t> kidx = as_const(m.kidx);
   for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kThreads64, SMALL ? 4 : 2) void k_ace_rank64(
     {
       const int t = lane & (kT64 - 1);
       const double* At = A + t * m.apad;
-      for (int g = wave; g < P.ngrp; g += kMixWaves) {
+      for (int g = wave; g < P.ngrp; g += kRank64Waves) {
         const int4 mem = mem_lds[g * (64 / kT64) + lane / kT64];
         const int key = uni(mem.w);
         if (mem.x < 0) continue;
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kThreads64, SMALL ? 4 : 2) void k_ace_rank64(
         }
       }
       // phi by Euler's theorem: A.Z over the A rows plus twice the constant row
-      if (wave == kMixWaves - 1) {
+      if (wave == kRank64Waves - 1) {
         const int t = lane >> 4;
         double sa = 0.0;
         if (P.arow)
