@@ -1031,6 +1031,32 @@ static ap_status upload_table(Ctx* ctx, const ap_table& t, TableDev* d, const ch
   return AP_OK;
 }
 
+// Interval cubics of the knot sum sum_i a_i (d_i - r)^3 Theta(d_i - r).
+static void fold_knots(int n, const double* a, const double* d, KnotDev* out) {
+  std::vector<double> D;
+  for (int i = 0; i < n; ++i)
+    if (!std::isnan(d[i])) D.push_back(d[i]);
+  std::sort(D.begin(), D.end());
+  D.erase(std::unique(D.begin(), D.end()), D.end());
+  const int m = (int)D.size();
+  *out = KnotDev{};
+  out->n = m;
+  out->n4 = (m + 3) / 4 * 4;
+  for (int k = 0; k < kMaxEamKnots; ++k) out->knot[k] = k < m ? D[k] : INFINITY;
+  for (int k = 0; k < m; ++k) {
+    long double s[4] = {0, 0, 0, 0};
+    for (int i = 0; i < n; ++i) {
+      if (!(d[i] >= D[k])) continue;
+      const long double g = (long double)d[i] - (long double)D[k], ai = a[i];
+      s[0] += ai * g * g * g;
+      s[1] += 3 * ai * g * g;
+      s[2] += 3 * ai * g;
+      s[3] += ai;
+    }
+    for (int q = 0; q < 4; ++q) out->c[k][q] = (double)s[q];
+  }
+}
+
 static ap_status check_nl(Ctx* ctx, const ap_nlist* nl) {
   if (!nl || !nl->nbr || !nl->count) return fail(ctx, AP_ERR_ARG, "neighbour list arrays missing");
   if (nl->capacity < 1 || nl->capacity > kMaxCap) return fail(ctx, AP_ERR_ARG, "capacity must be in [1, 256]");
@@ -1113,7 +1139,7 @@ ap_status ap_destroy(ap_ctx* c) {
                     &C.chunk_lo_d, &C.chunk_hi_d, &C.sys_chunk_d})
     release(*b);
   for (Buffer* b : {&ctx->cell_big, &ctx->pos4, &ctx->cell_count, &ctx->cell_start, &ctx->cell_cursor, &ctx->cell_atoms,
-                    &ctx->cell_pos, &ctx->cell_of, &ctx->scan_tmp, &ctx->wfp, &ctx->eF, &ctx->wgt,
+                    &ctx->cell_pos, &ctx->cell_of, &ctx->scan_tmp, &ctx->wfp, &ctx->eF,
                     &ctx->vir_atom, &ctx->e_tmp, &ctx->ace_row, &ctx->pair_g, &ctx->ace_counter,
                     &ctx->ace_rows_list, &ctx->ace_halo, &ctx->nbr_ace, &ctx->partials, &ctx->flags, &ctx->ind_atom, &ctx->mix_A,
                     &ctx->mix_om, &ctx->mix_phi, &ctx->mix_bn, &ctx->sw_csp, &ctx->sw_mu0,
@@ -1241,7 +1267,7 @@ ap_status ap_eam_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
   const int64_t N = sv.n_atoms;
   if (N > 0 && (!pos || !e_atom || !force)) return fail(ctx, AP_ERR_ARG, "pos/e_atom/force is NULL");
   if ((st = ensure(ctx, ctx->wfp, 8 * (size_t)N)) || (st = ensure(ctx, ctx->eF, 8 * (size_t)N)) ||
-      (st = ensure(ctx, ctx->wgt, 8 * (size_t)N)) || (st = ensure(ctx, ctx->e_eam_raw, 8 * (size_t)N)) ||
+      (st = ensure(ctx, ctx->e_eam_raw, 8 * (size_t)N)) ||
       (virial && (st = ensure(ctx, ctx->vir_atom, 72 * (size_t)N))))
     return st;
   const bool acc = flags == AP_ACCUMULATE;
@@ -1249,10 +1275,10 @@ ap_status ap_eam_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
   {
   PhaseTimer timer(ctx, AP_PHASE_EAM, s);
   if ((st = ensure(ctx, ctx->pos4, 32 * (size_t)std::max<int64_t>(N, 1)))) return st;
-  AP_HIP(launch_pack_pos((int32_t)N, pos, (double4*)ctx->pos4.p, s));
-  AP_HIP(launch_eam(*ctx, sv, pos, (const double4*)ctx->pos4.p, nl->nbr, nl->count, (int32_t)N,
-                    lambda, (double*)ctx->wfp.p, (double*)ctx->eF.p, (double*)ctx->wgt.p, e_atom,
-                    force, vir, acc, (double*)ctx->e_eam_raw.p, s));
+  AP_HIP(launch_pack_pos((int32_t)N, pos, lambda, (double4*)ctx->pos4.p, s));
+  AP_HIP(launch_eam(*ctx, sv, (const double4*)ctx->pos4.p, nl->nbr, nl->count, (int32_t)N,
+                    (double*)ctx->wfp.p, (double*)ctx->eF.p, e_atom, force, vir, acc,
+                    (double*)ctx->e_eam_raw.p, s));
   }
   // in a fused evaluation the ACE call reduces the EAM and ACE per-atom virials together
   if (virial && !ctx->fused_eval && (st = reduce_into(ctx, sv, vir, 9, virial, acc, s))) return st;
@@ -1291,7 +1317,7 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
   if (vir && !vir_acc) AP_HIP(launch_fill_f64(vir, 0.0, 9 * N, s));
   if ((st = ensure(ctx, ctx->pos4, 32 * (size_t)std::max<int64_t>(N, 1)))) return st;
   // a fused evaluation's EAM call packed these positions already
-  if (!ctx->fused_eval) AP_HIP(launch_pack_pos((int32_t)N, pos, (double4*)ctx->pos4.p, s));
+  if (!ctx->fused_eval) AP_HIP(launch_pack_pos((int32_t)N, pos, nullptr, (double4*)ctx->pos4.p, s));
   AP_HIP(launch_ace_rows((int32_t)N, ace_list, n_ace, (int32_t*)ctx->ace_row.p, s));
   // the ACE kernels stamp the listed atoms and their neighbours (the atoms the
   // gather visits) in the halo array with a fresh stamp per evaluation; a new
@@ -1501,16 +1527,8 @@ ap_status ap_set_eam_analytic(ap_ctx* c, const ap_eam_analytic* e) {
     return fail(ctx, AP_ERR_ARG, "analytic EAM: need a_zbl, eps0 > 0 and 0 < r_lo <= r_hi");
   EamAnalyticDev& p = ctx->ean;
   p = EamAnalyticDev{};
-  p.n_phi = e->n_phi;
-  p.n_rho = e->n_rho;
-  for (int i = 0; i < e->n_phi; ++i) {
-    p.a_phi[i] = e->a_phi[i];
-    p.d_phi[i] = e->d_phi[i];
-  }
-  for (int i = 0; i < e->n_rho; ++i) {
-    p.a_rho[i] = e->a_rho[i];
-    p.d_rho[i] = e->d_rho[i];
-  }
+  fold_knots(e->n_phi, e->a_phi, e->d_phi, &p.phi);
+  fold_knots(e->n_rho, e->a_rho, e->d_rho, &p.rho);
   p.r_cut_rho = e->r_cut_rho;
   double zc = 0.0;
   for (int i = 0; i < e->n_rho; ++i) {

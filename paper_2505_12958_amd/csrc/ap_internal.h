@@ -54,10 +54,14 @@ struct TableDev {
 
 // the paper's W EAM in closed form (passed to the EAM kernels by value)
 constexpr int kMaxEamKnots = 32;
+// a knot sum as cubics between its sorted distinct knots
+struct KnotDev {
+  int32_t n, n4;                    // distinct knots; padded to a multiple of 4
+  double knot[kMaxEamKnots];        // ascending, padded with +inf
+  double c[kMaxEamKnots + 1][4];    // interval below knot[k] (k = n: zero): powers of knot[k] - r
+};
 struct EamAnalyticDev {
-  int32_t n_phi, n_rho;
-  double a_phi[kMaxEamKnots], d_phi[kMaxEamKnots];
-  double a_rho[kMaxEamKnots], d_rho[kMaxEamKnots];
+  KnotDev phi, rho;
   double r_cut_rho, zeta_cut;       // zeta = zeta_0(max(r, r_cut)); zeta_cut = zeta_0(r_cut)
   double a_xi1, a_xi2, d_xi;
   double zbl_pref, a_zbl;           // Z^2 / (4 pi eps0), screening length
@@ -253,7 +257,7 @@ struct Ctx {
   Buffer cell_big, pos4;               // cell_big: [m, atoms of the cells too big for LDS]
   Buffer cell_count, cell_start, cell_cursor, cell_atoms, cell_pos, cell_of;
   Buffer scan_tmp;
-  Buffer wfp, eF, wgt, vir_atom, e_tmp;
+  Buffer wfp, eF, vir_atom, e_tmp;
   Buffer ace_row, pair_g, ace_counter, ace_rows_list, ace_halo, nbr_ace;
   int32_t halo_stamp = 0;           // last stamp written into ace_halo (0: cleared)
   Buffer mix_A, mix_om, mix_phi;        // mixed path: A, adjoint (2 sets), phi per ACE atom
@@ -376,12 +380,12 @@ hipError_t launch_switching(const SysView& sv, const double* pos, const int32_t*
                             int32_t* scan_tmp, double* lambda, int32_t* ace_list, int32_t* n_ace,
                             hipStream_t s);
 // EAM (k_eam.hip)
-hipError_t launch_pack_pos(int32_t n, const double* pos, double4* p4, hipStream_t s);
-hipError_t launch_eam(const Ctx& c, const SysView& sv, const double* pos, const double4* pos4,
-                      const int32_t* nbr,
-                      const int32_t* count, int32_t n_atoms, const double* lambda, double* wfp,
-                      double* eF, double* wgt, double* e_atom, double* force, double* vir_atom,
-                      bool accumulate, double* e_raw, hipStream_t s);
+// p4 = position and, in w, the EAM weight 1 - lambda (1 when lambda is NULL)
+hipError_t launch_pack_pos(int32_t n, const double* pos, const double* lambda, double4* p4,
+                           hipStream_t s);
+hipError_t launch_eam(const Ctx& c, const SysView& sv, const double4* pos4, const int32_t* nbr,
+                      const int32_t* count, int32_t n_atoms, double* wfp, double* eF, double* e_atom,
+                      double* force, double* vir_atom, bool accumulate, double* e_raw, hipStream_t s);
 // ACE (k_ace.hip)
 size_t ace_lds_bytes(const AceDev& a, int precision);
 hipError_t launch_ace_reset(int32_t* counter, hipStream_t s);

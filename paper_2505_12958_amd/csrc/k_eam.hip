@@ -5,6 +5,9 @@
 #include "ap_internal.h"
 #include "geom.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace ap {
 
 // coef: the table's (n-1) double4 coefficients, in global memory or staged in LDS
@@ -35,33 +38,44 @@ __device__ __forceinline__ void tab_eval(const TableDev& t, const double4* coef,
 // ---- the paper's W EAM in closed form (appendix "AP potential for tungsten":
 // equations eam_F_Marinica, eam_Phi_Marinica, eam_rho_Marinica,
 // tungsten_rho_up, tungsten_F_up, tungsten_Phi_up), FP64.
-__device__ __forceinline__ void an_knots(const double* a, const double* d, int n, double r, double& v,
+// A knot sum sum_i a_i (d_i - r)^3 Theta(d_i - r) as the cubic of r's interval
+// between the sorted distinct knots D_0 < D_1 < ...: for D_{k-1} < r <= D_k it is
+// c0 + t (c1 + t (c2 + t c3)) with t = D_k - r, the coefficients expanded on the
+// host in extended precision (KnotDev).  Adding up the knots one by one kept
+// the vector units busy (511 instructions per bond of the force pass); the
+// interval search is one compare and one add per knot.  Against extended
+// precision the W pair function's error falls from 1.2e-14 (its knots cancel)
+// to 6e-17, the density's from 9e-17 to 7e-17.
+__device__ __forceinline__ void an_knots(const KnotDev& d, const double4* coef, double r, double& v,
                                          double& dv) {
-  v = 0.0;
-  dv = 0.0;
-  for (int i = 0; i < n; ++i) {
-    const double t = d[i] - r;
-    if (t >= 0.0) {
-      const double t2 = t * t;
-      v += a[i] * t2 * t;
-      dv -= 3.0 * a[i] * t2;
-    }
+  int k = 0;
+  for (int i = 0; i < d.n4; i += 4) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) k += d.knot[i + q] < r ? 1 : 0;  // padded with +inf
   }
+  const double4 c = coef[k];
+  // (beyond the last knot the coefficients are zero)
+  const double t = reinterpret_cast<const double*>(coef + d.n + 1)[k] - r;
+  v = c.x + t * (c.y + t * (c.z + t * c.w));
+  dv = -(c.y + t * (2.0 * c.z + t * 3.0 * c.w));
 }
 
 // zeta(r) = zeta_0(max(r, r_cut))
-__device__ __forceinline__ void an_density(const EamAnalyticDev& p, double r, double& v, double& dv) {
+__device__ __forceinline__ void an_density(const EamAnalyticDev& p, const double4* coef, double r,
+                                           double& v, double& dv) {
+  an_knots(p.rho, coef, r, v, dv);
   if (r <= p.r_cut_rho) {
     v = p.zeta_cut;
     dv = 0.0;
-  } else {
-    an_knots(p.a_rho, p.d_rho, p.n_rho, r, v, dv);
   }
 }
 
 // Phi^Fit(r): screened Coulomb below r_lo, quintic bridge up to r_hi, knot sum above
-__device__ __forceinline__ void an_pair(const EamAnalyticDev& p, double r, double& v, double& dv) {
-  if (r < p.r_lo) {
+__device__ __forceinline__ void an_pair(const EamAnalyticDev& p, const double4* coef, double r, double& v,
+                                        double& dv) {
+  if (r > p.r_hi) {
+    an_knots(p.phi, coef, r, v, dv);
+  } else if (r < p.r_lo) {
     const double x = r / p.a_zbl;
     double s = 0.0, ds = 0.0;
     for (int k = 0; k < 4; ++k) {
@@ -71,12 +85,10 @@ __device__ __forceinline__ void an_pair(const EamAnalyticDev& p, double r, doubl
     }
     v = p.zbl_pref * s / r;
     dv = p.zbl_pref * (ds / r - s / (r * r));
-  } else if (r <= p.r_hi) {
+  } else {
     const double* b = p.b_phi;
     v = b[0] + r * (b[1] + r * (b[2] + r * (b[3] + r * (b[4] + r * b[5]))));
     dv = b[1] + r * (2.0 * b[2] + r * (3.0 * b[3] + r * (4.0 * b[4] + r * 5.0 * b[5])));
-  } else {
-    an_knots(p.a_phi, p.d_phi, p.n_phi, r, v, dv);
   }
 }
 
@@ -87,72 +99,108 @@ __device__ __forceinline__ void an_embed(const EamAnalyticDev& p, double x, doub
   dv = (x > 0.0 ? 0.5 * p.a_xi1 / s : 0.0) + 2.0 * p.a_xi2 * x;
 }
 
-// Copies a table's coefficients into LDS (whole workgroup, before any thread
-// leaves); returns where the bond loop reads them from.
-__device__ __forceinline__ const double4* stage_table(const TableDev& t, double4* lds, bool use) {
-  const double4* g = reinterpret_cast<const double4*>(t.c);
-  if (!use) return g;
-  for (int q = threadIdx.x; q < t.n - 1; q += blockDim.x) lds[q] = g[q];
+// The interval cubics of a knot sum, then its knots (0 behind the last), to LDS.
+__device__ __forceinline__ const double4* stage_knots(const KnotDev& d, double4* lds) {
+  for (int q = threadIdx.x; q <= d.n; q += blockDim.x) {
+    lds[q] = make_double4(d.c[q][0], d.c[q][1], d.c[q][2], d.c[q][3]);
+    reinterpret_cast<double*>(lds + d.n + 1)[q] = q < d.n ? d.knot[q] : 0.0;
+  }
   return lds;
+}
+// double4 records the staged knot sum takes
+__host__ __device__ inline int knot_records(const KnotDev& d) { return d.n + 1 + (d.n + 4) / 4; }
+
+// Copies n records of a table into LDS (whole workgroup, before any thread
+// leaves); returns where the bond loop reads them from.
+__device__ __forceinline__ const double4* stage_table(const double* c, int n, double4* lds, bool use) {
+  const double4* g = reinterpret_cast<const double4*>(c);
+  if (!use) return g;
+  for (int q = threadIdx.x; q < n; q += blockDim.x) lds[q] = g[q];
+  return lds;
+}
+
+// Sum over the LN parts of an atom's bonds: part p of the block's atom a sits
+// in thread p * (256 / LN) + a, so that neighbouring lanes read neighbouring
+// atoms of the slot-major list; the parts are added in order through LDS, and
+// the result is valid in part 0.
+template <int LN, int NV>
+__device__ __forceinline__ void sum_parts(double (&v)[NV], double* lds) {
+  if constexpr (LN > 1) {
+    constexpr int kAtoms = 256 / LN;
+    __syncthreads();  // the table staging shares this region
+#pragma unroll
+    for (int q = 0; q < NV; ++q) lds[q * 256 + threadIdx.x] = v[q];
+    __syncthreads();
+    if (threadIdx.x < kAtoms) {
+#pragma unroll
+      for (int q = 0; q < NV; ++q)
+        for (int p = 1; p < LN; ++p) v[q] += lds[q * 256 + p * kAtoms + threadIdx.x];
+    }
+  }
 }
 
 // kOrtho: every system is orthorhombic, so the box edges are hoisted out of
 // the bond loop (same arithmetic as the general displacement).  kLds: the
 // pair tables are staged in LDS (dynamic shared memory sized by the host).
-template <bool kOrtho, bool kLds, bool kAn>
+// LN threads share an atom's bonds (thread part, part + LN, ...).  pos4: the
+// position and, in w, the atom's EAM weight 1 - lambda.
+template <bool kOrtho, bool kLds, bool kAn, int LN>
 __global__ __launch_bounds__(256) void k_eam_density(SysView sv, TableDev rho_t, TableDev F_t,
                                                      EamAnalyticDev an,
                                                      const double4* __restrict__ pos4,
                                                      const int32_t* __restrict__ nbr,
                                                      const int32_t* __restrict__ count,
-                                                     const double* __restrict__ lambda,
                                                      double* __restrict__ wfp,
-                                                     double* __restrict__ eF,
-                                                     double* __restrict__ wgt) {
+                                                     double* __restrict__ eF) {
   extern __shared__ double4 tab_lds[];
-  const double4* rho_c = stage_table(rho_t, tab_lds, kLds);
-  if (kLds) __syncthreads();
+  const double4* rho_c = kAn ? stage_knots(an.rho, tab_lds)
+                             : stage_table(rho_t.c, rho_t.n - 1, tab_lds, kLds);
+  if (kLds || kAn) __syncthreads();
   const int n = sv.n_atoms;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double w = lambda ? 1.0 - lambda[i] : 1.0;
-  wgt[i] = w;
+  constexpr int kAtoms = 256 / LN;
+  const int i = blockIdx.x * kAtoms + threadIdx.x % kAtoms, part = threadIdx.x / kAtoms;
+  const bool live = i < n;
+  const double4 pi = live ? pos4[i] : make_double4(0.0, 0.0, 0.0, 0.0);
+  const double w = pi.w;
+  double rho[1] = {0.0};
+  if (w > 0.0) {
+    const int s = sv.sys_of[i];
+    const bool ortho = sv.ortho[s] != 0;
+    const double* H = sv.H + 9 * s;
+    const double* Hi = sv.Hi + 9 * s;
+    const double Lx = H[0], Ly = H[4], Lz = H[8];
+    const int c = count[i];
+#pragma unroll 2
+    for (int q = part; q < c; q += LN) {
+      const int j = nbr[(int64_t)q * n + i];
+      const double4 pj = pos4[j];
+      double dx, dy, dz;
+      if (kOrtho)
+        displacement_ortho(sv.per, Lx, Ly, Lz, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
+      else
+        displacement(ortho, H, Hi, sv.per, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
+      const double r = sqrt(dx * dx + dy * dy + dz * dz);
+      double v, dv;
+      if constexpr (kAn) an_density(an, rho_c, r, v, dv);
+      else tab_eval(rho_t, rho_c, r, false, v, dv);
+      rho[0] += v;
+    }
+  }
+  sum_parts<LN>(rho, reinterpret_cast<double*>(tab_lds));
+  if (!live || part != 0) return;
   if (!(w > 0.0)) {
     wfp[i] = 0.0;
     eF[i] = 0.0;
     return;
   }
-  const int s = sv.sys_of[i];
-  const bool ortho = sv.ortho[s] != 0;
-  const double* H = sv.H + 9 * s;
-  const double* Hi = sv.Hi + 9 * s;
-  const double Lx = H[0], Ly = H[4], Lz = H[8];
-  const double4 pi = pos4[i];
-  const int c = count[i];
-  double rho = 0.0;
-#pragma unroll 2
-  for (int q = 0; q < c; ++q) {
-    const int j = nbr[(int64_t)q * n + i];
-    const double4 pj = pos4[j];
-    double dx, dy, dz;
-    if (kOrtho)
-      displacement_ortho(sv.per, Lx, Ly, Lz, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
-    else
-      displacement(ortho, H, Hi, sv.per, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
-    const double r = sqrt(dx * dx + dy * dy + dz * dz);
-    double v, dv;
-    if constexpr (kAn) an_density(an, r, v, dv);
-    else tab_eval(rho_t, rho_c, r, false, v, dv);
-    rho += v;
-  }
   double Fv, Fp;
-  if constexpr (kAn) an_embed(an, rho, Fv, Fp);
-  else tab_eval(F_t, reinterpret_cast<const double4*>(F_t.c), rho, true, Fv, Fp);
+  if constexpr (kAn) an_embed(an, rho[0], Fv, Fp);
+  else tab_eval(F_t, reinterpret_cast<const double4*>(F_t.c), rho[0], true, Fv, Fp);
   wfp[i] = w * Fp;
   eF[i] = Fv;
 }
 
-template <bool kOrtho, bool kLds, bool kAn>
+template <bool kOrtho, bool kLds, bool kAn, int LN>
 __global__ __launch_bounds__(256) void k_eam_force(SysView sv, TableDev rho_t, TableDev phi_t,
                                                    EamAnalyticDev an,
                                                    const double4* __restrict__ pos4,
@@ -160,63 +208,72 @@ __global__ __launch_bounds__(256) void k_eam_force(SysView sv, TableDev rho_t, T
                                                    const int32_t* __restrict__ count,
                                                    const double* __restrict__ wfp,
                                                    const double* __restrict__ eF,
-                                                   const double* __restrict__ wgt,
                                                    double* __restrict__ e_atom,
                                                    double* __restrict__ force,
                                                    double* __restrict__ vir, int accumulate,
                                                    double* __restrict__ e_raw) {
   extern __shared__ double4 tab_lds[];
-  const double4* rho_c = stage_table(rho_t, tab_lds, kLds);
-  const double4* phi_c = stage_table(phi_t, tab_lds + (rho_t.n - 1), kLds);
-  if (kLds) __syncthreads();
+  const double4* rho_c = kAn ? stage_knots(an.rho, tab_lds)
+                             : stage_table(rho_t.c, rho_t.n - 1, tab_lds, kLds);
+  const double4* phi_c = kAn ? stage_knots(an.phi, tab_lds + knot_records(an.rho))
+                             : stage_table(phi_t.c, phi_t.n - 1, tab_lds + (rho_t.n - 1), kLds);
+  if (kLds || kAn) __syncthreads();
   const int n = sv.n_atoms;
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const int s = sv.sys_of[k];
-  const bool ortho = sv.ortho[s] != 0;
-  const double* H = sv.H + 9 * s;
-  const double* Hi = sv.Hi + 9 * s;
-  const double Lx = H[0], Ly = H[4], Lz = H[8];
-  const double4 pk = pos4[k];
-  const double wk = wgt[k], fk = wfp[k];
-  const int c = count[k];
-  double fx = 0, fy = 0, fz = 0, ephi = 0;
-  // atom k's bond gradients are parallel to the bonds, so its virial
-  // -sum_j d (x) G_kj is symmetric: six sums
-  double v00 = 0, v01 = 0, v02 = 0, v11 = 0, v12 = 0, v22 = 0;
+  constexpr int kAtoms = 256 / LN;
+  const int k = blockIdx.x * kAtoms + threadIdx.x % kAtoms, part = threadIdx.x / kAtoms;
+  const bool live = k < n;
+  // force, pair energy and virial sums; atom k's bond gradients are parallel to
+  // the bonds, so its virial -sum_j d (x) G_kj is symmetric: six sums
+  double a10[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  double wk = 0.0;
+  if (live) {
+    const int s = sv.sys_of[k];
+    const bool ortho = sv.ortho[s] != 0;
+    const double* H = sv.H + 9 * s;
+    const double* Hi = sv.Hi + 9 * s;
+    const double Lx = H[0], Ly = H[4], Lz = H[8];
+    const double4 pk = pos4[k];
+    wk = pk.w;
+    const double fk = wfp[k];
+    const int c = count[k];
 #pragma unroll 2
-  for (int q = 0; q < c; ++q) {
-    const int j = nbr[(int64_t)q * n + k];
-    const double wj = wgt[j], fj = wfp[j];
-    if (wk == 0.0 && wj == 0.0) continue;
-    const double4 pj = pos4[j];
-    double dx, dy, dz;
-    if (kOrtho)
-      displacement_ortho(sv.per, Lx, Ly, Lz, pk.x, pk.y, pk.z, pj.x, pj.y, pj.z, dx, dy, dz);
-    else
-      displacement(ortho, H, Hi, sv.per, pk.x, pk.y, pk.z, pj.x, pj.y, pj.z, dx, dy, dz);
-    const double r = sqrt(dx * dx + dy * dy + dz * dz);
-    const double ir = 1.0 / r;
-    double z, dzr, p, dp;
-    if constexpr (kAn) {
-      an_density(an, r, z, dzr);
-      an_pair(an, r, p, dp);
-    } else {
-      tab_eval(rho_t, rho_c, r, false, z, dzr);
-      tab_eval(phi_t, phi_c, r, false, p, dp);
+    for (int q = part; q < c; q += LN) {
+      const int j = nbr[(int64_t)q * n + k];
+      const double4 pj = pos4[j];
+      const double wj = pj.w, fj = wfp[j];
+      if (wk == 0.0 && wj == 0.0) continue;
+      double dx, dy, dz;
+      if (kOrtho)
+        displacement_ortho(sv.per, Lx, Ly, Lz, pk.x, pk.y, pk.z, pj.x, pj.y, pj.z, dx, dy, dz);
+      else
+        displacement(ortho, H, Hi, sv.per, pk.x, pk.y, pk.z, pj.x, pj.y, pj.z, dx, dy, dz);
+      const double r = sqrt(dx * dx + dy * dy + dz * dz);
+      const double ir = 1.0 / r;
+      double z, dzr, p, dp;
+      if constexpr (kAn) {
+        an_density(an, rho_c, r, z, dzr);
+        an_pair(an, phi_c, r, p, dp);
+      } else {
+        tab_eval(rho_t, rho_c, r, false, z, dzr);
+        tab_eval(phi_t, phi_c, r, false, p, dp);
+      }
+      const double a = ((fk + fj) * dzr + 0.5 * (wk + wj) * dp) * ir;
+      a10[0] += a * dx;
+      a10[1] += a * dy;
+      a10[2] += a * dz;
+      a10[3] += p;
+      // virial of atom k's own bond gradient G_kj = (w_k xi'_k zeta' + w_k Phi'/2) d/r
+      const double g = (fk * dzr + 0.5 * wk * dp) * ir;
+      const double gx = g * dx, gy = g * dy, gz = g * dz;
+      a10[4] -= dx * gx; a10[5] -= dx * gy; a10[6] -= dx * gz;
+      a10[7] -= dy * gy; a10[8] -= dy * gz;
+      a10[9] -= dz * gz;
     }
-    const double a = ((fk + fj) * dzr + 0.5 * (wk + wj) * dp) * ir;
-    fx += a * dx;
-    fy += a * dy;
-    fz += a * dz;
-    ephi += p;
-    // virial of atom k's own bond gradient G_kj = (w_k xi'_k zeta' + w_k Phi'/2) d/r
-    const double g = (fk * dzr + 0.5 * wk * dp) * ir;
-    const double gx = g * dx, gy = g * dy, gz = g * dz;
-    v00 -= dx * gx; v01 -= dx * gy; v02 -= dx * gz;
-    v11 -= dy * gy; v12 -= dy * gz;
-    v22 -= dz * gz;
   }
+  sum_parts<LN>(a10, reinterpret_cast<double*>(tab_lds));
+  if (!live || part != 0) return;
+  const double fx = a10[0], fy = a10[1], fz = a10[2], ephi = a10[3];
+  const double v00 = a10[4], v01 = a10[5], v02 = a10[6], v11 = a10[7], v12 = a10[8], v22 = a10[9];
   const double e_un = wk > 0.0 ? eF[k] + 0.5 * ephi : 0.0;  // E_k^EAM, unweighted
   const double e = wk > 0.0 ? wk * e_un : 0.0;
   if (e_raw) e_raw[k] = e_un;
@@ -238,35 +295,53 @@ __global__ __launch_bounds__(256) void k_eam_force(SysView sv, TableDev rho_t, T
   }
 }
 
-hipError_t launch_eam(const Ctx& c, const SysView& sv, const double* pos, const double4* pos4,
-                      const int32_t* nbr,
-                      const int32_t* count, int32_t n_atoms, const double* lambda, double* wfp,
-                      double* eF, double* wgt, double* e_atom, double* force, double* vir_atom,
-                      bool accumulate, double* e_raw, hipStream_t s) {
+// Threads per atom.  An atom's 58 or so bonds are one chain of gathers, square
+// roots and divisions: while the chip is not full, splitting it sets the time
+// (us, density + force pass, against one thread per atom: tables, 2,000 atoms
+// 31 + 42 -> 6.8 + 8.8 with 16 threads; 31,250 atoms 32 + 47 -> 13.3 + 20.2 with
+// 4, 12.6 + 25.1 with 16; 108,000 atoms 36 + 71 -> 25.2 + 51.7 with 4, 31 + 79
+// with 16).  A full chip is bound by the gathered 32-byte records, and the
+// split only shortens each block's chain: 250,000 atoms 54.8 + 114.6 with one
+// thread, 52.9 + 109.7 with 2, 54.4 + 117 with 4; 2.66 million 631 + 1516,
+// 641 + 1406, 680 + 1387.  Closed form, 1.27 million atoms: 421 + 699, 354 + 683,
+// 336 + 699 (418 + 958 when the knots were added up one by one).
+constexpr int kEamSplit16 = 8192, kEamSplit4 = 131072;
+
+hipError_t launch_eam(const Ctx& c, const SysView& sv, const double4* pos4, const int32_t* nbr,
+                      const int32_t* count, int32_t n_atoms, double* wfp, double* eF, double* e_atom,
+                      double* force, double* vir_atom, bool accumulate, double* e_raw, hipStream_t s) {
   if (n_atoms == 0) return hipSuccess;
-  const dim3 g((n_atoms + 255) / 256), b(256);
-  (void)pos;
   // pair tables in LDS when both fit in a quarter of a CU's LDS (four
   // resident workgroups); otherwise they are read through the caches
-  const size_t rho_b = c.eam_analytic ? 0 : 32 * (size_t)(c.rho.n - 1);
-  const size_t phi_b = c.eam_analytic ? 0 : 32 * (size_t)(c.phi.n - 1);
-  const bool lds = !c.eam_analytic && rho_b + phi_b <= 40 * 1024;
-  auto go = [&](auto dens, auto frc) {
-    hipLaunchKernelGGL(dens, g, b, lds ? rho_b : 0, s, sv, c.rho, c.F, c.ean, pos4, nbr, count, lambda,
-                       wfp, eF, wgt);
-    hipLaunchKernelGGL(frc, g, b, lds ? rho_b + phi_b : 0, s, sv, c.rho, c.phi, c.ean, pos4, nbr, count,
-                       wfp, eF, wgt, e_atom, force, vir_atom, accumulate ? 1 : 0, e_raw);
+  // (the closed form's interval cubics, at most 42 records each, always are)
+  const size_t rho_b = 32 * (size_t)(c.eam_analytic ? knot_records(c.ean.rho) : c.rho.n - 1);
+  const size_t phi_b = 32 * (size_t)(c.eam_analytic ? knot_records(c.ean.phi) : c.phi.n - 1);
+  const bool lds = c.eam_analytic || rho_b + phi_b <= 40 * 1024;
+  auto go = [&](auto dens, auto frc, int ln) {
+    const dim3 g((unsigned)(((int64_t)n_atoms * ln + 255) / 256)), b(256);
+    // the parts' sums reuse the region: 1 and 10 doubles per thread
+    const size_t pd = ln > 1 ? 8 * 256 : 0, pf = ln > 1 ? 80 * 256 : 0;
+    hipLaunchKernelGGL(dens, g, b, std::max(lds ? rho_b : 0, pd), s, sv, c.rho, c.F, c.ean, pos4, nbr,
+                       count, wfp, eF);
+    hipLaunchKernelGGL(frc, g, b, std::max(lds ? rho_b + phi_b : 0, pf), s, sv, c.rho, c.phi, c.ean, pos4,
+                       nbr, count, wfp, eF, e_atom, force, vir_atom, accumulate ? 1 : 0, e_raw);
   };
-  if (c.eam_analytic) {
-    if (sv.all_ortho) go(k_eam_density<true, false, true>, k_eam_force<true, false, true>);
-    else go(k_eam_density<false, false, true>, k_eam_force<false, false, true>);
-  } else if (sv.all_ortho) {
-    if (lds) go(k_eam_density<true, true, false>, k_eam_force<true, true, false>);
-    else go(k_eam_density<true, false, false>, k_eam_force<true, false, false>);
-  } else {
-    if (lds) go(k_eam_density<false, true, false>, k_eam_force<false, true, false>);
-    else go(k_eam_density<false, false, false>, k_eam_force<false, false, false>);
-  }
+  auto pick = [&](auto ln) {
+    constexpr int LN = decltype(ln)::value;
+    if (c.eam_analytic) {
+      if (sv.all_ortho) go(k_eam_density<true, false, true, LN>, k_eam_force<true, false, true, LN>, LN);
+      else go(k_eam_density<false, false, true, LN>, k_eam_force<false, false, true, LN>, LN);
+    } else if (sv.all_ortho) {
+      if (lds) go(k_eam_density<true, true, false, LN>, k_eam_force<true, true, false, LN>, LN);
+      else go(k_eam_density<true, false, false, LN>, k_eam_force<true, false, false, LN>, LN);
+    } else {
+      if (lds) go(k_eam_density<false, true, false, LN>, k_eam_force<false, true, false, LN>, LN);
+      else go(k_eam_density<false, false, false, LN>, k_eam_force<false, false, false, LN>, LN);
+    }
+  };
+  if (n_atoms <= kEamSplit16) pick(std::integral_constant<int, 16>{});
+  else if (n_atoms <= kEamSplit4) pick(std::integral_constant<int, 4>{});
+  else pick(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

@@ -436,16 +436,18 @@ hipError_t launch_check_finite(int32_t n, const double* force, int32_t* flag, hi
 }
 
 // --------------------------------------------------------------------------
-// positions as one 32-byte record per atom: a neighbour's position is one
-// gathered load instead of three
-__global__ void k_pack_pos(int n, const double* __restrict__ pos, double4* __restrict__ p4) {
+// position and EAM weight as one 32-byte record per atom: a neighbour is one
+// gathered load instead of three or four
+__global__ void k_pack_pos(int n, const double* __restrict__ pos, const double* __restrict__ lambda,
+                           double4* __restrict__ p4) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p4[i] = make_double4(pos[i], pos[n + i], pos[2 * n + i], 0.0);
+  if (i < n) p4[i] = make_double4(pos[i], pos[n + i], pos[2 * n + i], lambda ? 1.0 - lambda[i] : 1.0);
 }
 
-hipError_t launch_pack_pos(int32_t n, const double* pos, double4* p4, hipStream_t s) {
+hipError_t launch_pack_pos(int32_t n, const double* pos, const double* lambda, double4* p4,
+                           hipStream_t s) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pack_pos, dim3((n + 255) / 256), dim3(256), 0, s, n, pos, p4);
+  hipLaunchKernelGGL(k_pack_pos, dim3((n + 255) / 256), dim3(256), 0, s, n, pos, lambda, p4);
   return hipGetLastError();
 }
 
