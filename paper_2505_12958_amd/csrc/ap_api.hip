@@ -1138,8 +1138,8 @@ ap_status ap_destroy(ap_ctx* c) {
   for (Buffer* b : {&C.off_d, &C.H_d, &C.Hi_d, &C.ortho_d, &C.grid_d, &C.cell_base_d, &C.sys_of_d,
                     &C.chunk_lo_d, &C.chunk_hi_d, &C.sys_chunk_d})
     release(*b);
-  for (Buffer* b : {&ctx->cell_big, &ctx->pos4, &ctx->cell_count, &ctx->cell_start, &ctx->cell_cursor, &ctx->cell_atoms,
-                    &ctx->cell_pos, &ctx->cell_of, &ctx->scan_tmp, &ctx->wfp, &ctx->eF,
+  for (Buffer* b : {&ctx->cell_big, &ctx->pos4, &ctx->cell_count, &ctx->cell_start, &ctx->cell_rank, &ctx->cell_atoms,
+                    &ctx->cell_pos, &ctx->cell_rel, &ctx->cell_of, &ctx->scan_tmp, &ctx->wfp, &ctx->eF,
                     &ctx->vir_atom, &ctx->e_tmp, &ctx->ace_row, &ctx->pair_g, &ctx->ace_counter,
                     &ctx->ace_rows_list, &ctx->ace_halo, &ctx->nbr_ace, &ctx->partials, &ctx->flags, &ctx->ind_atom, &ctx->mix_A,
                     &ctx->mix_om, &ctx->mix_phi, &ctx->mix_bn, &ctx->sw_csp, &ctx->sw_mu0,
@@ -1168,27 +1168,29 @@ ap_status ap_build_neighbors(ap_ctx* c, const ap_systems* sys, const double* pos
   const int nc = ctx->sys.n_cells;
   if ((st = ensure(ctx, ctx->cell_count, 4 * (size_t)nc)) ||
       (st = ensure(ctx, ctx->cell_start, 4 * (size_t)nc)) ||
-      (st = ensure(ctx, ctx->cell_cursor, 4 * (size_t)nc)) ||
+      (st = ensure(ctx, ctx->cell_rank, 4 * (size_t)N)) ||
       (st = ensure(ctx, ctx->cell_big, 4 * ((size_t)N + 1))) ||
       (st = ensure(ctx, ctx->cell_of, 4 * (size_t)N)) ||
       (st = ensure(ctx, ctx->cell_atoms, 4 * (size_t)N)) ||
       (st = ensure(ctx, ctx->cell_pos, 32 * (size_t)N)) ||
+      (st = ensure(ctx, ctx->cell_rel, 16 * (size_t)N)) ||
       (st = ensure(ctx, ctx->scan_tmp, 4 * ((size_t)std::max<int64_t>(nc, N) / 4096 + 2))))
     return st;
   int32_t* flags = (int32_t*)ctx->flags.p;
   PhaseTimer timer(ctx, AP_PHASE_NEIGHBORS, s);
   if (needed_capacity) AP_HIP(launch_fill_i32(flags, 0, 1, s));
   AP_HIP(launch_fill_i32((int32_t*)ctx->cell_count.p, 0, nc, s));
-  AP_HIP(launch_bin(sv, pos, (int32_t*)ctx->cell_of.p, (int32_t*)ctx->cell_count.p, s));
-  // the scan also writes the scatter's cursors (a copy of the cell starts)
+  AP_HIP(launch_bin(sv, pos, (int32_t*)ctx->cell_of.p, (int32_t*)ctx->cell_rank.p,
+                    (int32_t*)ctx->cell_count.p, s));
   AP_HIP(launch_scan_exclusive((const int32_t*)ctx->cell_count.p, (int32_t*)ctx->cell_start.p, nc,
-                               (int32_t*)ctx->scan_tmp.p, s, (int32_t*)ctx->cell_cursor.p));
-  AP_HIP(launch_scatter(sv, pos, (const int32_t*)ctx->cell_of.p, (int32_t*)ctx->cell_cursor.p,
-                        (int32_t*)ctx->cell_atoms.p, (double4*)ctx->cell_pos.p, s));
+                               (int32_t*)ctx->scan_tmp.p, s));
+  AP_HIP(launch_scatter(sv, pos, (const int32_t*)ctx->cell_of.p, (const int32_t*)ctx->cell_rank.p,
+                        (const int32_t*)ctx->cell_start.p, (int32_t*)ctx->cell_atoms.p, (double4*)ctx->cell_pos.p,
+                        (float4*)ctx->cell_rel.p, s));
   AP_HIP(launch_fill_nbr_cells(sv, nc, pos, (const int32_t*)ctx->cell_of.p,
                                (const int32_t*)ctx->cell_start.p, (const int32_t*)ctx->cell_count.p,
-                               (const double4*)ctx->cell_pos.p, nl->nbr, nl->count, nl->capacity,
-                               flags, (int32_t*)ctx->cell_big.p, s));
+                               (const double4*)ctx->cell_pos.p, (const float4*)ctx->cell_rel.p,
+                               nl->nbr, nl->count, nl->capacity, flags, (int32_t*)ctx->cell_big.p, s));
   if (nl->rev) AP_HIP(launch_rev((int32_t)N, nl->nbr, nl->count, nl->rev, s));
   ctx->cells_n_atoms = N;
   if (needed_capacity) {

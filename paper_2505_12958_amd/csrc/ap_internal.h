@@ -29,6 +29,14 @@ constexpr int kReduceChunk = 4096;         // atoms per deterministic partial su
 
 // --------------------------------------------------------------------------
 // device view of the systems of one call
+// Workgroups go to the eight XCDs in turn; this numbers them so that each XCD
+// gets one contiguous run of the work items, whose neighbours then share its L2.
+constexpr unsigned kXcds = 8;
+__host__ __device__ inline unsigned xcd_chunk(unsigned b, unsigned n) {
+  const unsigned q = n / kXcds, r = n % kXcds, x = b % kXcds;
+  return x * q + (x < r ? x : r) + b / kXcds;
+}
+
 struct SysView {
   int32_t n_sys;
   int32_t n_atoms;
@@ -255,7 +263,7 @@ struct Ctx {
   SysCache sys;
   // scratch, grown on demand
   Buffer cell_big, pos4;               // cell_big: [m, atoms of the cells too big for LDS]
-  Buffer cell_count, cell_start, cell_cursor, cell_atoms, cell_pos, cell_of;
+  Buffer cell_count, cell_start, cell_rank, cell_atoms, cell_pos, cell_rel, cell_of;
   Buffer scan_tmp;
   Buffer wfp, eF, vir_atom, e_tmp;
   Buffer ace_row, pair_g, ace_counter, ace_rows_list, ace_halo, nbr_ace;
@@ -324,21 +332,18 @@ ap_status ensure(Ctx* ctx, Buffer& b, size_t bytes);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t* p, uint8_t v, int64_t n, hipStream_t s);
-hipError_t launch_bin(const SysView& sv, const double* pos, int32_t* cell_of, int32_t* cell_count,
-                      hipStream_t s);
+hipError_t launch_bin(const SysView& sv, const double* pos, int32_t* cell_of, int32_t* cell_rank,
+                      int32_t* cell_count, hipStream_t s);
 hipError_t launch_scan_exclusive(const int32_t* in, int32_t* out, int32_t n, int32_t* tmp,
-                                 hipStream_t s, int32_t* out2 = nullptr);
+                                 hipStream_t s);
 hipError_t launch_scatter(const SysView& sv, const double* pos, const int32_t* cell_of,
-                          int32_t* cursor, int32_t* cell_atoms, double4* cell_pos, hipStream_t s);
+                          const int32_t* cell_rank, const int32_t* cell_start, int32_t* cell_atoms,
+                          double4* cell_pos, float4* cell_rel, hipStream_t s);
 hipError_t launch_fill_nbr_cells(const SysView& sv, int32_t n_cells, const double* pos,
                                  const int32_t* cell_of, const int32_t* cell_start,
-                                 const int32_t* cell_count, const double4* cell_pos, int32_t* nbr,
-                                 int32_t* count, int32_t cap, int32_t* overflow, int32_t* big_atoms,
-                                 hipStream_t s);
-hipError_t launch_fill_nbr(const SysView& sv, const double* pos, const int32_t* cell_of,
-                           const int32_t* cell_start, const int32_t* cell_count,
-                           const double4* cell_pos, int32_t* nbr, int32_t* count, int32_t cap,
-                           int32_t* overflow, hipStream_t s);
+                                 const int32_t* cell_count, const double4* cell_pos,
+                                 const float4* cell_rel, int32_t* nbr, int32_t* count, int32_t cap,
+                                 int32_t* overflow, int32_t* big_atoms, hipStream_t s);
 hipError_t launch_rev(int32_t n_atoms, const int32_t* nbr, const int32_t* count, int32_t* rev,
                       hipStream_t s);
 // switching and compaction (k_misc.hip)

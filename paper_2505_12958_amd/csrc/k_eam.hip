@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void k_eam_density(SysView sv, TableDev rho_t,
   if (kLds || kAn) __syncthreads();
   const int n = sv.n_atoms;
   constexpr int kAtoms = 256 / LN;
-  const int i = blockIdx.x * kAtoms + threadIdx.x % kAtoms, part = threadIdx.x / kAtoms;
+  const int i = xcd_chunk(blockIdx.x, gridDim.x) * kAtoms + threadIdx.x % kAtoms, part = threadIdx.x / kAtoms;
   const bool live = i < n;
   const double4 pi = live ? pos4[i] : make_double4(0.0, 0.0, 0.0, 0.0);
   const double w = pi.w;
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void k_eam_force(SysView sv, TableDev rho_t, T
   if (kLds || kAn) __syncthreads();
   const int n = sv.n_atoms;
   constexpr int kAtoms = 256 / LN;
-  const int k = blockIdx.x * kAtoms + threadIdx.x % kAtoms, part = threadIdx.x / kAtoms;
+  const int k = xcd_chunk(blockIdx.x, gridDim.x) * kAtoms + threadIdx.x % kAtoms, part = threadIdx.x / kAtoms;
   const bool live = k < n;
   // force, pair energy and virial sums; atom k's bond gradients are parallel to
   // the bonds, so its virial -sum_j d (x) G_kj is symmetric: six sums

@@ -62,8 +62,7 @@ __global__ __launch_bounds__(1024) void k_scan_sums(int32_t* __restrict__ sums, 
 template <int MODE>
 __global__ __launch_bounds__(kScanThreads) void k_tile_scan(const int32_t* __restrict__ in, int n,
                                                             const int32_t* __restrict__ offs,
-                                                            int32_t* __restrict__ out,
-                                                            int32_t* __restrict__ out2) {
+                                                            int32_t* __restrict__ out) {
   __shared__ int ws[kScanThreads / 64];
   const int base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
   int v[kScanItems];
@@ -87,7 +86,6 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(const int32_t* __res
     if (i < n) {
       if (MODE == 0) {
         out[i] = run;
-        if (out2) out2[i] = run;
       } else if (v[k]) {
         out[run] = i;
       }
@@ -97,7 +95,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(const int32_t* __res
 }
 
 static hipError_t scan_impl(const int32_t* in, int32_t n, int32_t* out, int32_t* total,
-                            int32_t* tmp, int mode, hipStream_t s, int32_t* out2 = nullptr) {
+                            int32_t* tmp, int mode, hipStream_t s) {
   const int nt = (n + kScanTile - 1) / kScanTile;
   if (nt == 0) {
     if (total) {
@@ -108,18 +106,16 @@ static hipError_t scan_impl(const int32_t* in, int32_t n, int32_t* out, int32_t*
   hipLaunchKernelGGL(k_tile_sums, dim3(nt), dim3(kScanThreads), 0, s, in, n, tmp);
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, tmp, nt, total);
   if (mode == 0)
-    hipLaunchKernelGGL(k_tile_scan<0>, dim3(nt), dim3(kScanThreads), 0, s, in, n, tmp, out, out2);
+    hipLaunchKernelGGL(k_tile_scan<0>, dim3(nt), dim3(kScanThreads), 0, s, in, n, tmp, out);
   else
-    hipLaunchKernelGGL(k_tile_scan<1>, dim3(nt), dim3(kScanThreads), 0, s, in, n, tmp, out,
-                       (int32_t*)nullptr);
+    hipLaunchKernelGGL(k_tile_scan<1>, dim3(nt), dim3(kScanThreads), 0, s, in, n, tmp, out);
   return hipGetLastError();
 }
 
-// tmp must hold ceil(n / 4096) + 1 ints; out2 (optional) receives a second
-// copy of the scan
+// tmp must hold ceil(n / 4096) + 1 ints
 hipError_t launch_scan_exclusive(const int32_t* in, int32_t* out, int32_t n, int32_t* tmp,
-                                 hipStream_t s, int32_t* out2) {
-  return scan_impl(in, n, out, nullptr, tmp, 0, s, out2);
+                                 hipStream_t s) {
+  return scan_impl(in, n, out, nullptr, tmp, 0, s);
 }
 
 hipError_t launch_compact(int32_t n, const int32_t* flag, int32_t* out_list, int32_t* out_n,

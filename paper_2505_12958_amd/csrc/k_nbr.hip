@@ -2,6 +2,7 @@
 // the canonical FP64 test, ascending-order ELL lists and the reverse-slot
 // index.  Also the generic fill and scan primitives.
 #include <algorithm>
+#include <type_traits>
 
 #include "ap_internal.h"
 #include "geom.h"
@@ -33,65 +34,92 @@ hipError_t launch_fill_u8(uint8_t* p, uint8_t v, int64_t n, hipStream_t s) { ret
 // --------------------------------------------------------------------------
 // cell of atom i: orthorhombic boxes bin Cartesian coordinates (clamped into
 // the grid in free dimensions), triclinic boxes bin wrapped fractional ones.
+// rel (where asked for): the position relative to the cell's centre, in FP32;
+// infinite where that is not the nearest image of an atom near its cell (see
+// k_fill_nbr_cell).
 __device__ __forceinline__ int cell_coords(const SysView& sv, int s, double x, double y, double z,
-                                           int& cx, int& cy, int& cz) {
+                                           float3* rel) {
   const int* g = sv.grid + 3 * s;
   const double* H = sv.H + 9 * s;
   double f0, f1, f2;
+  bool ok = true;
   if (sv.ortho[s]) {
     f0 = x / H[0];
     f1 = y / H[4];
     f2 = z / H[8];
+    ok = (!sv.per[0] || (f0 >= 0.0 && f0 < 1.0)) && (!sv.per[1] || (f1 >= 0.0 && f1 < 1.0)) &&
+         (!sv.per[2] || (f2 >= 0.0 && f2 < 1.0));
   } else {
     frac3(sv.Hi + 9 * s, x, y, z, f0, f1, f2);
+    ok = f0 >= -0.25 && f0 < 1.25 && f1 >= -0.25 && f1 < 1.25 && f2 >= -0.25 && f2 < 1.25;
     f0 -= floor(f0);
     f1 -= floor(f1);
     f2 -= floor(f2);
   }
   // non-finite coordinates land in cell 0 (the force check reports them)
-  cx = isfinite(f0) ? (int)fmax(-1.0, fmin(floor(f0 * g[0]), (double)g[0])) : 0;
-  cy = isfinite(f1) ? (int)fmax(-1.0, fmin(floor(f1 * g[1]), (double)g[1])) : 0;
-  cz = isfinite(f2) ? (int)fmax(-1.0, fmin(floor(f2 * g[2]), (double)g[2])) : 0;
+  int cx = isfinite(f0) ? (int)fmax(-1.0, fmin(floor(f0 * g[0]), (double)g[0])) : 0;
+  int cy = isfinite(f1) ? (int)fmax(-1.0, fmin(floor(f1 * g[1]), (double)g[1])) : 0;
+  int cz = isfinite(f2) ? (int)fmax(-1.0, fmin(floor(f2 * g[2]), (double)g[2])) : 0;
   cx = cx < 0 ? 0 : (cx >= g[0] ? g[0] - 1 : cx);
   cy = cy < 0 ? 0 : (cy >= g[1] ? g[1] - 1 : cy);
   cz = cz < 0 ? 0 : (cz >= g[2] ? g[2] - 1 : cz);
+  if (rel) {
+    const double a = f0 - (cx + 0.5) / g[0], b = f1 - (cy + 0.5) / g[1], c = f2 - (cz + 0.5) / g[2];
+    double rx = a * H[0], ry = b * H[4], rz = c * H[8];
+    if (!sv.ortho[s]) {
+      rx += b * H[3] + c * H[6];
+      ry += a * H[1] + c * H[7];
+      rz += a * H[2] + b * H[5];
+    }
+    *rel = ok ? make_float3((float)rx, (float)ry, (float)rz) : make_float3(INFINITY, INFINITY, INFINITY);
+  }
   return sv.cell_base[s] + (cx * g[1] + cy) * g[2] + cz;
 }
 
+// cell_rank: the atom's place in its cell, in the order of arrival.  Taken here,
+// where the count needs its atomic anyway, so that the scatter has none: both
+// kernels at 1.27 million atoms 34 + 105 us with a second atomic in the
+// scatter, 51 + 33 us so.
 __global__ void k_bin(SysView sv, const double* __restrict__ pos, int32_t* __restrict__ cell_of,
-                      int32_t* __restrict__ cell_count) {
+                      int32_t* __restrict__ cell_rank, int32_t* __restrict__ cell_count) {
   const int n = sv.n_atoms;
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  int cx, cy, cz;
-  int c = cell_coords(sv, sv.sys_of[i], pos[i], pos[n + i], pos[2 * n + i], cx, cy, cz);
+  const int c = cell_coords(sv, sv.sys_of[i], pos[i], pos[n + i], pos[2 * n + i], nullptr);
   cell_of[i] = c;
-  atomicAdd(&cell_count[c], 1);
+  cell_rank[i] = atomicAdd(&cell_count[c], 1);
 }
 
-hipError_t launch_bin(const SysView& sv, const double* pos, int32_t* cell_of, int32_t* cell_count,
-                      hipStream_t s) {
+hipError_t launch_bin(const SysView& sv, const double* pos, int32_t* cell_of, int32_t* cell_rank,
+                      int32_t* cell_count, hipStream_t s) {
   if (sv.n_atoms == 0) return hipSuccess;
   hipLaunchKernelGGL(k_bin, dim3((sv.n_atoms + 255) / 256), dim3(256), 0, s, sv, pos, cell_of,
-                     cell_count);
+                     cell_rank, cell_count);
   return hipGetLastError();
 }
 
-__global__ void k_scatter(int n, const double* __restrict__ pos, const int32_t* __restrict__ cell_of,
-                          int32_t* __restrict__ cursor, int32_t* __restrict__ cell_atoms,
-                          double4* __restrict__ cell_pos) {
+__global__ void k_scatter(SysView sv, const double* __restrict__ pos, const int32_t* __restrict__ cell_of,
+                          const int32_t* __restrict__ cell_rank,
+                          const int32_t* __restrict__ cell_start, int32_t* __restrict__ cell_atoms, double4* __restrict__ cell_pos,
+                          float4* __restrict__ cell_rel) {
+  const int n = sv.n_atoms;
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  int slot = atomicAdd(&cursor[cell_of[i]], 1);
+  const double x = pos[i], y = pos[n + i], z = pos[2 * n + i];
+  float3 r;
+  cell_coords(sv, sv.sys_of[i], x, y, z, &r);
+  const int slot = cell_start[cell_of[i]] + cell_rank[i];
   cell_atoms[slot] = i;
-  cell_pos[slot] = make_double4(pos[i], pos[n + i], pos[2 * n + i], (double)i);
+  cell_pos[slot] = make_double4(x, y, z, (double)i);
+  cell_rel[slot] = make_float4(r.x, r.y, r.z, __int_as_float(i));
 }
 
 hipError_t launch_scatter(const SysView& sv, const double* pos, const int32_t* cell_of,
-                          int32_t* cursor, int32_t* cell_atoms, double4* cell_pos, hipStream_t s) {
+                          const int32_t* cell_rank, const int32_t* cell_start, int32_t* cell_atoms,
+                          double4* cell_pos, float4* cell_rel, hipStream_t s) {
   if (sv.n_atoms == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter, dim3((sv.n_atoms + 255) / 256), dim3(256), 0, s, sv.n_atoms, pos,
-                     cell_of, cursor, cell_atoms, cell_pos);
+  hipLaunchKernelGGL(k_scatter, dim3((sv.n_atoms + 255) / 256), dim3(256), 0, s, sv, pos,
+                     cell_of, cell_rank, cell_start, cell_atoms, cell_pos, cell_rel);
   return hipGetLastError();
 }
 
@@ -198,23 +226,6 @@ __device__ __forceinline__ void atom_list_direct(const SysView& sv, const double
   if (lane == 0) count[i] = cnt < cap ? cnt : cap;
 }
 
-__global__ __launch_bounds__(256) void k_fill_nbr(SysView sv, const double* __restrict__ pos,
-                                                  const int32_t* __restrict__ cell_of,
-                                                  const int32_t* __restrict__ cell_start,
-                                                  const int32_t* __restrict__ cell_count,
-                                                  const double4* __restrict__ cell_pos,
-                                                  int32_t* __restrict__ nbr,
-                                                  int32_t* __restrict__ count, int cap,
-                                                  int32_t* __restrict__ overflow) {
-  __shared__ int list[kWavesPerBlock][kListLds];
-  __shared__ int st_cell[kWavesPerBlock][32];
-  __shared__ int st_pre[kWavesPerBlock][33];
-  const int i = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-  if (i >= sv.n_atoms) return;  // whole wavefront leaves together
-  atom_list_direct(sv, pos, cell_of, cell_start, cell_count, cell_pos, nbr, count, cap, overflow, i,
-                   list, st_cell, st_pre);
-}
-
 __global__ __launch_bounds__(256) void k_fill_nbr_big(SysView sv, const double* __restrict__ pos,
                                                       const int32_t* __restrict__ cell_of,
                                                       const int32_t* __restrict__ cell_start,
@@ -236,93 +247,167 @@ __global__ __launch_bounds__(256) void k_fill_nbr_big(SysView sv, const double* 
                      big_atoms[1 + w], list, st_cell, st_pre);
 }
 
-hipError_t launch_fill_nbr(const SysView& sv, const double* pos, const int32_t* cell_of,
-                           const int32_t* cell_start, const int32_t* cell_count,
-                           const double4* cell_pos, int32_t* nbr, int32_t* count, int32_t cap,
-                           int32_t* overflow, hipStream_t s) {
-  if (sv.n_atoms == 0) return hipSuccess;
-  const int blocks = (sv.n_atoms + kWavesPerBlock - 1) / kWavesPerBlock;
-  hipLaunchKernelGGL(k_fill_nbr, dim3(blocks), dim3(64 * kWavesPerBlock), 0, s, sv, pos, cell_of,
-                     cell_start, cell_count, cell_pos, nbr, count, cap, overflow);
-  return hipGetLastError();
+// --------------------------------------------------------------------------
+// Ascending sort of one value per lane over the wavefront: the bitonic network
+// on lane exchanges (DPP up to distance 8, row and half swaps beyond).
+template <int D>
+__device__ __forceinline__ void lane_pair(int v, int& lo, int& hi) {
+  int a = v, b;
+  if constexpr (D == 1) b = __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, true);        // quad_perm 1,0,3,2
+  else if constexpr (D == 2) b = __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xf, 0xf, true);   // quad_perm 2,3,0,1
+  else if constexpr (D == 4) {
+    b = __builtin_amdgcn_update_dpp(v, v, 0x1B, 0xf, 0xf, true);                            // quad_perm 3,2,1,0
+    b = __builtin_amdgcn_update_dpp(b, b, 0x141, 0xf, 0xf, true);                           // row_half_mirror
+  } else if constexpr (D == 8) b = __builtin_amdgcn_update_dpp(v, v, 0x128, 0xf, 0xf, true);  // row_ror 8
+  else {
+    const auto p = D == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)
+                           : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = (int)p[0];
+    b = (int)p[1];
+  }
+  lo = a < b ? a : b;
+  hi = a < b ? b : a;
+}
+
+// lanes that keep the smaller value of a pair at distance D in runs of S
+__host__ __device__ constexpr unsigned long long keep_low(int D, int S) {
+  unsigned long long m = 0;
+  for (int l = 0; l < 64; ++l)
+    if (((l & D) == 0) == ((l & S) == 0)) m |= 1ull << l;
+  return m;
+}
+
+template <int D, int S>
+__device__ __forceinline__ void sort_step(int& v) {
+  int lo, hi;
+  lane_pair<D>(v, lo, hi);
+  constexpr unsigned long long m = keep_low(D, S);
+  v = __builtin_amdgcn_inverse_ballot_w64(m) ? lo : hi;
+  if constexpr (D > 1) sort_step<D / 2, S>(v);
+}
+
+__device__ __forceinline__ int wave_sort(int v) {
+  sort_step<1, 2>(v);
+  sort_step<2, 4>(v);
+  sort_step<4, 8>(v);
+  sort_step<8, 16>(v);
+  sort_step<16, 32>(v);
+  sort_step<32, 64>(v);
+  return v;
 }
 
 // --------------------------------------------------------------------------
 // One workgroup per cell.  The candidates of the cell's stencil (at most 27
-// deduplicated cells) are gathered into LDS once (as FP32 coordinates) and
-// shared by the cell's atoms, one wavefront per atom: lanes screen 64
-// candidates at a time in FP32 with a 0.05 A margin and compact the
-// survivors (about a quarter); the survivors are tested with the canonical
-// FP64 rule, accepted indices are compacted into a per-wavefront LDS list
-// with a ballot, then each lane ranks its entries (indices are unique) and
-// stores them in ascending order.  A cell whose stencil holds more than
-// kMaxCand candidates falls back to the kernel above for its atoms.
+// deduplicated cells) are gathered into LDS once, as FP32 positions relative
+// to the cell's centre in the image next to it, and shared by the cell's
+// atoms, one wavefront per atom: lanes test 64 candidates at a time, accepted
+// indices are compacted into a per-wavefront LDS list, sorted across the lanes
+// (at most 64 of them; more are ranked in LDS) and stored in ascending order.
+//
+// The result is the canonical FP64 rule's (geom.h), bit for bit, though nearly
+// every pair is decided in FP32: a pair is accepted below r_c (1 - 2e-5) and
+// rejected beyond r_c (1 + 2e-5); between, the wavefront evaluates the rule
+// itself.  That is sound as long as
+//  - coordinates stay below 8 r_c, those relative to an atom's own cell (FP32,
+//    cell_rel) as well as the sums with the offset between the two cells: each
+//    is rounded by at most 8 r_c 2^-24, a distance is off by less than 1e-5 r_c;
+//  - every fractional coordinate lies in [-1/4, 5/4), so that the rule's single
+//    wrap yields the nearest image, and the atom in the cell of its wrapped
+//    position (orthorhombic boxes: in [0, 1), atoms outside are binned into the
+//    box's outer cells unwrapped);
+//  - the images agree, or both are out of reach.  With at least three cells
+//    along an axis the staged image differs from the nearest only where the
+//    two are a third of the box or more apart, at least one cell edge
+//    (> r_c) in either; with fewer cells the pair is wrapped again, and a pair
+//    within 1e-5 of half the box goes to the rule.
+// A workgroup that holds any candidate outside these limits takes the rule for
+// every pair.  A cell whose stencil holds more than kMaxCand candidates falls
+// back to the kernel above for its atoms.
+//
+// The instruction issue bounds it (per atom about 230 vector and 175 scalar
+// instructions; it was 412 vector with an FP32 screen that wrapped every pair,
+// an FP64 test of each survivor and the rank loop).  Cells are dealt to the XCDs
+// in contiguous runs, so that the 4-byte stores into the slot-major rows meet
+// in one L2.  us, before -> after: 250,000 atoms 202 -> 134, 1.27 million
+// 1032 -> 627, 2.66 million 2284 -> 1282, 96 sheared cells of 250 to 16,000 atoms
+// (the FP64 test of every candidate fell away) 620 -> 201.  Seven workgroups a
+// CU rather than six: 1282 against 1336 us at 2.66 million; eight spill.
 constexpr int kCellThreads = 256;
 constexpr int kCellWaves = kCellThreads / 64;
 constexpr int kMaxCand = 512;
 
-__global__ __launch_bounds__(kCellThreads) void k_fill_nbr_cell(
+__global__ __launch_bounds__(kCellThreads, 7) void k_fill_nbr_cell(
     SysView sv, const int32_t* __restrict__ cell_start, const int32_t* __restrict__ cell_count,
-    const double4* __restrict__ cell_pos, int32_t* __restrict__ nbr, int32_t* __restrict__ count,
-    int cap, int32_t* __restrict__ overflow, int32_t* __restrict__ big_atoms) {
-  // candidates as float (x, y, z) plus their cell-order index: the screen;
-  // the exact FP64 test reads the survivors' positions from cell_pos
-  __shared__ float4 cposf[kMaxCand];
-  __shared__ int cand[kCellWaves][kMaxCand];
-  __shared__ __align__(16) int list[kCellWaves][kListLds + 4];
-  __shared__ int st_src[32];   // first cell-ordered atom of each stencil cell
-  __shared__ int st_pre[33];   // exclusive prefix of the stencil cells' counts
+    const double4* __restrict__ cell_pos, const float4* __restrict__ cell_rel,
+    int32_t* __restrict__ nbr, int32_t* __restrict__ count, int cap, int32_t* __restrict__ overflow,
+    int32_t* __restrict__ big_atoms) {
+  __shared__ float4 cposf[kMaxCand];  // x, y, z; w: the atom's index
+  __shared__ int csrc[kMaxCand];      // its place in cell_pos
+  __shared__ __align__(16) int list[kCellWaves][kMaxCand + 4];
+  __shared__ float4 st_off[27];  // stencil cells: centre relative to this cell's; w: atoms
+  __shared__ int2 st_src[27];    // first cell-ordered atom, exclusive prefix of the counts
+  __shared__ int s_head[4];      // total, any candidate for the rule, system, home
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = blockIdx.x;
+  const int c = xcd_chunk(blockIdx.x, gridDim.x);
   const int n_here = cell_count[c];
   if (n_here == 0) return;  // whole workgroup
-  // system of this cell
-  int lo = 0, hi = sv.n_sys - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (sv.cell_base[mid] <= c) lo = mid; else hi = mid - 1;
-  }
-  const int s = lo;
-  const int* g = sv.grid + 3 * s;
-  const int ci = c - sv.cell_base[s];
-  const int cc[3] = {ci / (g[1] * g[2]), (ci / g[2]) % g[1], ci % g[2]};
   if (wave == 0) {
-    int my_cell = -1, my_cnt = 0, my_src = 0;
+    // system of this cell
+    int lo = 0, hi = sv.n_sys - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (sv.cell_base[mid] <= c) lo = mid; else hi = mid - 1;
+    }
+    const int s = lo;
+    const int* g = sv.grid + 3 * s;
+    const double* H = sv.H + 9 * s;
+    const int ci = c - sv.cell_base[s];
+    const int cc[3] = {ci / (g[1] * g[2]), (ci / g[2]) % g[1], ci % g[2]};
+    int my_cnt = 0, home = 0;
     if (lane < 27) {
       const int idx[3] = {lane / 9, (lane / 3) % 3, lane % 3};
-      int co[3];
+      int co[3], my_src = 0;
+      double o[3];
       bool ok = true;
       for (int k = 0; k < 3; ++k) {
         const int gk = g[k];
-        if (sv.per[k] && gk < 3) {
-          if (idx[k] >= gk) ok = false;
-          co[k] = idx[k];
-        } else {
-          int v = cc[k] + idx[k] - 1;
-          if (sv.per[k]) {
-            v = v < 0 ? v + gk : (v >= gk ? v - gk : v);
-          } else if (v < 0 || v >= gk) {
-            ok = false;
-          }
-          co[k] = v;
+        const bool few = sv.per[k] && gk < 3;  // the stencil is the whole axis
+        home = 3 * home + (few ? cc[k] : 1);
+        int v = few ? idx[k] : cc[k] + idx[k] - 1;
+        o[k] = (double)(v - cc[k]) / gk;
+        if (few) {
+          if (v >= gk) ok = false;
+        } else if (sv.per[k]) {
+          v = v < 0 ? v + gk : (v >= gk ? v - gk : v);
+        } else if (v < 0 || v >= gk) {
+          ok = false;
         }
+        co[k] = v;
       }
       if (ok) {
-        my_cell = sv.cell_base[s] + (co[0] * g[1] + co[1]) * g[2] + co[2];
+        const int my_cell = sv.cell_base[s] + (co[0] * g[1] + co[1]) * g[2] + co[2];
         my_cnt = cell_count[my_cell];
         my_src = cell_start[my_cell];
       }
+      // (off-diagonal entries of an orthorhombic box are zero)
+      st_off[lane] = make_float4((float)(o[0] * H[0] + o[1] * H[3] + o[2] * H[6]),
+                                 (float)(o[0] * H[1] + o[1] * H[4] + o[2] * H[7]),
+                                 (float)(o[0] * H[2] + o[1] * H[5] + o[2] * H[8]),
+                                 __int_as_float(my_cnt));
+      st_src[lane].x = my_src;
     }
     const int incl = wave_incl_scan_i32(my_cnt, lane);
-    if (lane < 27) {
-      st_src[lane] = my_src;
-      st_pre[lane] = incl - my_cnt;
+    if (lane < 27) st_src[lane].y = incl - my_cnt;
+    if (lane == 0) {
+      s_head[1] = 0;
+      s_head[2] = s;
+      s_head[3] = home;
     }
-    if (lane == 26) st_pre[27] = incl;
+    if (lane == 26) s_head[0] = incl;
   }
   __syncthreads();
-  const int total = st_pre[27];
+  const int total = __builtin_amdgcn_readfirstlane(s_head[0]);
   const int n = sv.n_atoms;
   const int first = cell_start[c];
   if (total > kMaxCand) {
@@ -336,92 +421,121 @@ __global__ __launch_bounds__(kCellThreads) void k_fill_nbr_cell(
       big_atoms[1 + s_base + a] = (int)cell_pos[first + a].w;
     return;
   }
-  // candidates of the stencil, cell after cell, all loads of the workgroup in
-  // one pass: candidate q belongs to the last stencil cell k with
-  // st_pre[k] <= q (that cell is not empty, as st_pre[k + 1] > q)
-  for (int q = tid; q < total; q += kCellThreads) {
-    int lo = 0, hi = 26;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (st_pre[mid] <= q) lo = mid; else hi = mid - 1;
+  // candidates, cell after cell, 16 threads to a stencil cell; the last batch
+  // of 64 is padded with positions that pass no comparison
+  {
+    const float rc2 = (float)sv.rc2, reach2 = 64.f * rc2;
+    bool exact = false;
+    for (int k = tid >> 4; k < 27; k += kCellThreads / 16) {
+      const float4 o = st_off[k];
+      const int2 src = st_src[k];
+      for (int q = tid & 15; q < __float_as_int(o.w); q += 16) {
+        const float4 r = cell_rel[src.x + q];
+        const float x = r.x + o.x, y = r.y + o.y, z = r.z + o.z;
+        const float big = fmaxf(fmaxf(fmaxf(r.x * r.x, r.y * r.y), fmaxf(r.z * r.z, x * x)),
+                                fmaxf(y * y, z * z));
+        exact = exact || !(big < reach2) || isnan(x) || isnan(y) || isnan(z);
+        cposf[src.y + q] = make_float4(x, y, z, r.w);
+        csrc[src.y + q] = src.x + q;
+      }
     }
-    const int src = st_src[lo] + (q - st_pre[lo]);
-    const double4 p = cell_pos[src];
-    cposf[q] = make_float4((float)p.x, (float)p.y, (float)p.z, __int_as_float(src));
+    const int pad = ((total + 63) & ~63) - total;
+    if (tid < pad) cposf[total + tid] = make_float4(NAN, NAN, NAN, __int_as_float(-1));
+    if (exact) s_head[1] = 1;
   }
   __syncthreads();
+  const bool exact = __builtin_amdgcn_readfirstlane(s_head[1]) != 0;
+  const int s = __builtin_amdgcn_readfirstlane(s_head[2]);
+  const int self0 = __builtin_amdgcn_readfirstlane(st_src[s_head[3]].y);
   const bool ortho = sv.ortho[s] != 0;
+  const int* g = sv.grid + 3 * s;
   const double* H = sv.H + 9 * s;
   const double* Hi = sv.Hi + 9 * s;
-  // screen in FP32 on orthorhombic boxes: the minimum-image distance of the
-  // rounded positions is within 0.02 A of the exact one for coordinates below
-  // 1e5 A, so every pair with r < r_c passes r < r_c + 0.05 A; the exact
-  // canonical FP64 test then decides (triclinic boxes: every candidate goes on)
-  const float Lf[3] = {(float)H[0], (float)H[4], (float)H[8]};
-  const float iLf[3] = {1.f / Lf[0], 1.f / Lf[1], 1.f / Lf[2]};
-  const float rs = (float)sqrt(sv.rc2) + 0.05f;
-  const float rs2 = rs * rs;
+  const bool few[3] = {sv.per[0] && g[0] < 3, sv.per[1] && g[1] < 3, sv.per[2] && g[2] < 3};
+  const float near2 = (float)(sv.rc2 * ((1.0 - 2e-5) * (1.0 - 2e-5)));
+  const float far2 = (float)(sv.rc2 * ((1.0 + 2e-5) * (1.0 + 2e-5)));
+  // the pair's wrap along the few-cell axes: fractional rows and lattice vectors
+  const bool wrap = few[0] || few[1] || few[2];
+  __shared__ float s_wrap[3][6];
+  if (wrap) {
+    if (tid < 9) {
+      const int k = tid / 3, x = tid % 3;
+      s_wrap[k][x] = ortho ? (k == x ? 1.f / (float)H[4 * k] : 0.f) : (float)Hi[3 * x + k];
+      s_wrap[k][3 + x] = (float)H[3 * k + x];
+    }
+    __syncthreads();
+  }
   int* lw = list[wave];
-  int* cw = cand[wave];
-  for (int a = wave; a < n_here; a += kCellWaves) {
-    const double4 pi = cell_pos[first + a];
-    const int i = (int)pi.w;
-    const float xf = (float)pi.x, yf = (float)pi.y, zf = (float)pi.z;
-    int npass = 0;
+  // the accepted candidates of the cell's atom a, in candidate order: their
+  // number.  kMode 0: pairs in FP32; 1: after the wrap along the few-cell axes;
+  // 2: every pair by the rule
+  auto scan = [&](auto mode, int a) {
+    constexpr int kMode = decltype(mode)::value;
+    const float4 me = cposf[self0 + a];
+    const int i = __float_as_int(me.w);
+    int cnt = 0;
     for (int base = 0; base < total; base += 64) {
-      const int q = base + lane;
-      bool pass = false;
-      int src = 0;
-      if (q < total) {
-        const float4 pf = cposf[q];
-        src = __float_as_int(pf.w);
-        if (ortho) {
-          float d[3] = {pf.x - xf, pf.y - yf, pf.z - zf};
+      const float4 pf = cposf[base + lane];
+      const int j = __float_as_int(pf.w);
+      unsigned long long in = 0, open = ~0ull;
+      if constexpr (kMode < 2) {
+        float dx = pf.x - me.x, dy = pf.y - me.y, dz = pf.z - me.z;
+        bool edge = false;
+        if constexpr (kMode == 1) {
 #pragma unroll
           for (int k = 0; k < 3; ++k)
-            if (sv.per[k]) d[k] -= Lf[k] * rintf(d[k] * iLf[k]);
-          pass = d[0] * d[0] + d[1] * d[1] + d[2] * d[2] < rs2;
-        } else {
-          pass = true;
+            if (few[k]) {
+              const float* w = s_wrap[k];
+              const float t = w[0] * dx + w[1] * dy + w[2] * dz, u = rintf(t);
+              edge = edge || fabsf(t - u) > 0.49999f;
+              dx -= u * w[3];
+              dy -= u * w[4];
+              dz -= u * w[5];
+            }
         }
+        const float r2 = dx * dx + dy * dy + dz * dz;
+        in = __ballot(r2 < near2);
+        open = __ballot(r2 < far2) & ~in;
+        if constexpr (kMode == 1) open |= __ballot(edge);
       }
-      const unsigned long long b = __ballot(pass);
-      if (pass) cw[npass + __popcll(b & ((1ull << lane) - 1ull))] = src;
-      npass += __popcll(b);
-    }
-    __syncwarp_ap();
-    int cnt = 0;
-    for (int base = 0; base < npass; base += 64) {
-      const int q = base + lane;
-      bool acc = false;
-      int j = -1;
-      if (q < npass) {
-        const double4 pj = cell_pos[cw[q]];
-        j = (int)pj.w;
-        if (j != i) {
-          double dx, dy, dz;
-          displacement(ortho, H, Hi, sv.per, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
-          acc = norm2(dx, dy, dz) < sv.rc2;
+      if (open) {
+        bool acc = false;
+        if ((open >> lane & 1) && base + lane < total) {
+          const double4 pi = cell_pos[first + a], pj = cell_pos[csrc[base + lane]];
+          double ex, ey, ez;
+          displacement(ortho, H, Hi, sv.per, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, ex, ey, ez);
+          acc = norm2(ex, ey, ez) < sv.rc2;
         }
+        in = (in & ~open) | __ballot(acc);
       }
-      const unsigned long long b = __ballot(acc);
-      if (acc) {
-        const int p = cnt + __popcll(b & ((1ull << lane) - 1ull));
-        if (p < kListLds) lw[p] = j;
-      }
-      cnt += __popcll(b);
+      in &= __ballot(j != i);
+      if (__builtin_amdgcn_inverse_ballot_w64(in))
+        lw[__builtin_amdgcn_mbcnt_hi((unsigned)(in >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in, cnt))] = j;
+      cnt += __popcll(in);
     }
-    const int m = cnt < kListLds ? cnt : kListLds;
-    if (lane < 4) lw[m + lane] = 0x7fffffff;  // sentinels: the rank loop reads whole int4
-    __syncwarp_ap();
-    for (int e = lane; e < m; e += 64) {
-      const int v = lw[e];
-      int rank = 0;
-      for (int q = 0; q < m; q += 4) {
-        const int4 u = *reinterpret_cast<const int4*>(lw + q);
-        rank += (u.x < v) + (u.y < v) + (u.z < v) + (u.w < v);
+    return cnt;
+  };
+  for (int a = wave; a < n_here; a += kCellWaves) {
+    const int i = __builtin_amdgcn_readfirstlane(__float_as_int(cposf[self0 + a].w));
+    const int cnt = exact  ? scan(std::integral_constant<int, 2>{}, a)
+                    : wrap ? scan(std::integral_constant<int, 1>{}, a)
+                           : scan(std::integral_constant<int, 0>{}, a);
+    if (cnt <= 64) {
+      __syncwarp_ap();
+      const int v = wave_sort(lane < cnt ? lw[lane] : 0x7fffffff);
+      if (lane < (cnt < cap ? cnt : cap)) nbr[(int64_t)lane * n + i] = v;
+    } else {
+      if (lane < 4) lw[cnt + lane] = 0x7fffffff;  // sentinels: the rank loop reads whole int4
+      __syncwarp_ap();
+      for (int e = lane; e < cnt; e += 64) {
+        const int v = lw[e];
+        int rank = 0;
+        for (int q = 0; q < cnt; q += 4) {
+          const int4 u = *reinterpret_cast<const int4*>(lw + q);
+          rank += (u.x < v) + (u.y < v) + (u.z < v) + (u.w < v);
+        }
+        if (rank < cap) nbr[(int64_t)rank * n + i] = v;
       }
-      if (rank < cap) nbr[(int64_t)rank * n + i] = v;
     }
     if (lane == 0) {
       count[i] = cnt < cap ? cnt : cap;
@@ -433,14 +547,14 @@ __global__ __launch_bounds__(kCellThreads) void k_fill_nbr_cell(
 
 hipError_t launch_fill_nbr_cells(const SysView& sv, int32_t n_cells, const double* pos,
                                  const int32_t* cell_of, const int32_t* cell_start,
-                                 const int32_t* cell_count, const double4* cell_pos, int32_t* nbr,
-                                 int32_t* count, int32_t cap, int32_t* overflow, int32_t* big_atoms,
-                                 hipStream_t s) {
+                                 const int32_t* cell_count, const double4* cell_pos,
+                                 const float4* cell_rel, int32_t* nbr, int32_t* count, int32_t cap,
+                                 int32_t* overflow, int32_t* big_atoms, hipStream_t s) {
   if (sv.n_atoms == 0 || n_cells == 0) return hipSuccess;
   hipError_t e = launch_fill_i32(big_atoms, 0, 1, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_fill_nbr_cell, dim3(n_cells), dim3(kCellThreads), 0, s, sv, cell_start,
-                     cell_count, cell_pos, nbr, count, cap, overflow, big_atoms);
+                     cell_count, cell_pos, cell_rel, nbr, count, cap, overflow, big_atoms);
   const int blocks = std::min((sv.n_atoms + kWavesPerBlock - 1) / kWavesPerBlock, 1024);
   hipLaunchKernelGGL(k_fill_nbr_big, dim3(blocks), dim3(64 * kWavesPerBlock), 0, s, sv, pos, cell_of,
                      cell_start, cell_count, cell_pos, nbr, count, cap, overflow, big_atoms);
