@@ -204,6 +204,8 @@ static ap_status prepare_systems(Ctx* ctx, const ap_systems* sys, SysView* sv) {
     C.cutoff = sys->cutoff;
     C.n_cells = (int32_t)cells;
     C.n_chunks = (int32_t)lo.size();
+    C.one_chunk_each = true;
+    for (int s = 0; s < ns; ++s) C.one_chunk_each = C.one_chunk_each && sc[s + 1] - sc[s] == 1;
     C.all_ortho = std::all_of(ortho.begin(), ortho.end(), [](uint8_t o) { return o != 0; });
     C.valid = true;
   }
@@ -1178,8 +1180,8 @@ ap_status ap_build_neighbors(ap_ctx* c, const ap_systems* sys, const double* pos
     return st;
   int32_t* flags = (int32_t*)ctx->flags.p;
   PhaseTimer timer(ctx, AP_PHASE_NEIGHBORS, s);
-  if (needed_capacity) AP_HIP(launch_fill_i32(flags, 0, 1, s));
-  AP_HIP(launch_fill_i32((int32_t*)ctx->cell_count.p, 0, nc, s));
+  AP_HIP(launch_clear_nbr(nc, (int32_t*)ctx->cell_count.p, (int32_t*)ctx->cell_big.p,
+                          needed_capacity ? flags : nullptr, s));
   AP_HIP(launch_bin(sv, pos, (int32_t*)ctx->cell_of.p, (int32_t*)ctx->cell_rank.p,
                     (int32_t*)ctx->cell_count.p, s));
   AP_HIP(launch_scan_exclusive((const int32_t*)ctx->cell_count.p, (int32_t*)ctx->cell_start.p, nc,
@@ -1247,7 +1249,7 @@ static ap_status reduce_into(Ctx* ctx, const SysView& sv, const double* vals, in
   ap_status st;
   PhaseTimer timer(ctx, AP_PHASE_REDUCE, s);
   if ((st = scratch_reduce(ctx, m))) return st;
-  AP_HIP(launch_reduce(sv, ctx->sys.n_chunks, (const int64_t*)ctx->sys.chunk_lo_d.p,
+  AP_HIP(launch_reduce(sv, ctx->sys.n_chunks, ctx->sys.one_chunk_each, (const int64_t*)ctx->sys.chunk_lo_d.p,
                        (const int64_t*)ctx->sys.chunk_hi_d.p, (const int32_t*)ctx->sys.sys_chunk_d.p,
                        vals, m, sv.n_atoms, (double*)ctx->partials.p, out, accumulate, s, copy0,
                        copy1));
@@ -1313,14 +1315,13 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
     return st;
   const bool acc = flags == AP_ACCUMULATE;
   double* vir = virial ? (double*)ctx->vir_atom.p : nullptr;
-  if (!acc) AP_HIP(launch_fill_f64(e_atom, 0.0, N, s));
   // a fused evaluation adds the ACE per-atom virial to the EAM call's
   const bool vir_acc = vir && ctx->fused_eval;
-  if (vir && !vir_acc) AP_HIP(launch_fill_f64(vir, 0.0, 9 * N, s));
   if ((st = ensure(ctx, ctx->pos4, 32 * (size_t)std::max<int64_t>(N, 1)))) return st;
   // a fused evaluation's EAM call packed these positions already
-  if (!ctx->fused_eval) AP_HIP(launch_pack_pos((int32_t)N, pos, nullptr, (double4*)ctx->pos4.p, s));
-  AP_HIP(launch_ace_rows((int32_t)N, ace_list, n_ace, (int32_t*)ctx->ace_row.p, s));
+  AP_HIP(launch_ace_prep((int32_t)N, pos, ace_list, n_ace, (int32_t*)ctx->ace_row.p,
+                         acc ? nullptr : e_atom, vir_acc ? nullptr : vir,
+                         ctx->fused_eval ? nullptr : (double4*)ctx->pos4.p, s));
   // the ACE kernels stamp the listed atoms and their neighbours (the atoms the
   // gather visits) in the halo array with a fresh stamp per evaluation; a new
   // allocation, or the stamp running out of range, clears it once.  A stale

@@ -233,6 +233,7 @@ struct SysCache {
   double cutoff = 0;
   int32_t n_cells = 0;
   int32_t n_chunks = 0;
+  bool one_chunk_each = false;
   bool all_ortho = false;
   // device
   Buffer off_d, H_d, Hi_d, ortho_d, grid_d, cell_base_d, sys_of_d;
@@ -332,6 +333,8 @@ ap_status ensure(Ctx* ctx, Buffer& b, size_t bytes);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t* p, uint8_t v, int64_t n, hipStream_t s);
+hipError_t launch_clear_nbr(int32_t n_cells, int32_t* cell_count, int32_t* big_atoms, int32_t* flag,
+                            hipStream_t s);
 hipError_t launch_bin(const SysView& sv, const double* pos, int32_t* cell_of, int32_t* cell_rank,
                       int32_t* cell_count, hipStream_t s);
 hipError_t launch_scan_exclusive(const int32_t* in, int32_t* out, int32_t n, int32_t* tmp,
@@ -353,7 +356,7 @@ hipError_t launch_compact(int32_t n, const int32_t* flag, int32_t* out_list, int
                           int32_t* tmp, hipStream_t s);
 hipError_t launch_seq(int32_t n, int32_t* out, hipStream_t s);
 // reductions
-hipError_t launch_reduce(const SysView& sv, int32_t n_chunks, const int64_t* chunk_lo,
+hipError_t launch_reduce(const SysView& sv, int32_t n_chunks, bool one_chunk_each, const int64_t* chunk_lo,
                          const int64_t* chunk_hi, const int32_t* sys_chunk, const double* vals,
                          int32_t m, int64_t stride, double* partials, double* out, bool accumulate,
                          hipStream_t s, double* copy0 = nullptr, double* copy1 = nullptr);
@@ -451,7 +454,8 @@ hipError_t launch_ace_gather(const Ctx& c, int32_t n_atoms, const int32_t* nbr, 
                              const int32_t* rev, const int32_t* nbr_ace, int32_t cap,
                              const int32_t* ace_row, const int32_t* halo, int32_t stamp,
                              const void* pair_g, double* force, bool accumulate, hipStream_t s);
-hipError_t launch_ace_rows(int32_t n_atoms, const int32_t* ace_list, const int32_t* n_ace,
-                           int32_t* ace_row, hipStream_t s);
+hipError_t launch_ace_prep(int32_t n_atoms, const double* pos, const int32_t* ace_list,
+                           const int32_t* n_ace, int32_t* ace_row, double* e_atom, double* vir,
+                           double4* p4, hipStream_t s);
 
 }  // namespace ap

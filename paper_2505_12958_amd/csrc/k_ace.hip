@@ -293,12 +293,27 @@ __global__ void k_ace_rows(int n, const int32_t* __restrict__ ace_list,
   if (t < m) row[ace_list ? ace_list[t] : t] = t;
 }
 
-hipError_t launch_ace_rows(int32_t n_atoms, const int32_t* ace_list, const int32_t* n_ace,
-                           int32_t* ace_row, hipStream_t s) {
-  hipError_t e = launch_fill_i32(ace_row, -1, n_atoms, s);
-  if (e != hipSuccess || n_atoms == 0) return e;
-  hipLaunchKernelGGL(k_ace_rows, dim3((n_atoms + 255) / 256), dim3(256), 0, s, n_atoms, ace_list,
-                     n_ace, ace_row);
+// what the call starts from, in one launch: no atom listed and, where given,
+// zero energies and virials and the packed positions (weight 1)
+__global__ void k_ace_prep(int n, const double* __restrict__ pos, int32_t* __restrict__ row,
+                           double* __restrict__ e_atom, double* __restrict__ vir,
+                           double4* __restrict__ p4) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  row[i] = -1;
+  if (e_atom) e_atom[i] = 0.0;
+  if (vir)
+    for (int64_t k = 0; k < 9; ++k) vir[k * n + i] = 0.0;
+  if (p4) p4[i] = make_double4(pos[i], pos[n + i], pos[2 * n + i], 1.0);
+}
+
+hipError_t launch_ace_prep(int32_t n_atoms, const double* pos, const int32_t* ace_list,
+                           const int32_t* n_ace, int32_t* ace_row, double* e_atom, double* vir,
+                           double4* p4, hipStream_t s) {
+  if (n_atoms == 0) return hipSuccess;
+  const dim3 g((n_atoms + 255) / 256), b(256);
+  hipLaunchKernelGGL(k_ace_prep, g, b, 0, s, n_atoms, pos, ace_row, e_atom, vir, p4);
+  hipLaunchKernelGGL(k_ace_rows, g, b, 0, s, n_atoms, ace_list, n_ace, ace_row);
   return hipGetLastError();
 }
 

@@ -76,6 +76,24 @@ __device__ __forceinline__ int cell_coords(const SysView& sv, int s, double x, d
   return sv.cell_base[s] + (cx * g[1] + cy) * g[2] + cz;
 }
 
+// what a neighbour build counts in: cells, the fallback list, the overflow flag
+__global__ void k_clear_nbr(int n_cells, int32_t* __restrict__ cell_count, int32_t* __restrict__ big_atoms,
+                            int32_t* __restrict__ flag) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n_cells) cell_count[i] = 0;
+  if (i == 0) {
+    big_atoms[0] = 0;
+    if (flag) *flag = 0;
+  }
+}
+
+hipError_t launch_clear_nbr(int32_t n_cells, int32_t* cell_count, int32_t* big_atoms, int32_t* flag,
+                            hipStream_t s) {
+  hipLaunchKernelGGL(k_clear_nbr, dim3((n_cells + 255) / 256), dim3(256), 0, s, n_cells, cell_count,
+                     big_atoms, flag);
+  return hipGetLastError();
+}
+
 // cell_rank: the atom's place in its cell, in the order of arrival.  Taken here,
 // where the count needs its atomic anyway, so that the scatter has none: both
 // kernels at 1.27 million atoms 34 + 105 us with a second atomic in the
@@ -551,8 +569,6 @@ hipError_t launch_fill_nbr_cells(const SysView& sv, int32_t n_cells, const doubl
                                  const float4* cell_rel, int32_t* nbr, int32_t* count, int32_t cap,
                                  int32_t* overflow, int32_t* big_atoms, hipStream_t s) {
   if (sv.n_atoms == 0 || n_cells == 0) return hipSuccess;
-  hipError_t e = launch_fill_i32(big_atoms, 0, 1, s);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_fill_nbr_cell, dim3(n_cells), dim3(kCellThreads), 0, s, sv, cell_start,
                      cell_count, cell_pos, cell_rel, nbr, count, cap, overflow, big_atoms);
   const int blocks = std::min((sv.n_atoms + kWavesPerBlock - 1) / kWavesPerBlock, 1024);
