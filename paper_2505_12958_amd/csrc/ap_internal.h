@@ -37,6 +37,15 @@ __host__ __device__ inline unsigned xcd_chunk(unsigned b, unsigned n) {
   return x * q + (x < r ? x : r) + b / kXcds;
 }
 
+// The same in runs of `run` workgroups: where the work sits in a part of the
+// grid that the host doesn't know, every XCD still gets its share.
+__host__ __device__ inline unsigned xcd_runs(unsigned b, unsigned n, unsigned run) {
+  const unsigned group = kXcds * run, g0 = b / group * group;
+  if (g0 + group > n) return b;
+  const unsigned r = b - g0;
+  return g0 + r % kXcds * run + r / kXcds;
+}
+
 struct SysView {
   int32_t n_sys;
   int32_t n_atoms;

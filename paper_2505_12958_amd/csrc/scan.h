@@ -33,6 +33,36 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
   return v;
 }
 
+// Sums over the wavefront of up to 16 values at once: the first four exchanges
+// halve the number of values a lane holds (13 exchanges for nine values instead
+// of 54).  Lane l returns the sum of value 8 (l>>2&1) + 4 (l>>3&1) + 2 (l>>4&1)
+// + (l>>5&1).
+template <int NV>
+__device__ __forceinline__ double wave_sums_f64(const double (&v)[NV], int lane) {
+  static_assert(NV > 8 && NV <= 16, "nine to sixteen values");
+  double t[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) t[q] = q < NV ? v[q] : 0.0;
+#pragma unroll
+  for (int step = 0; step < 4; ++step) {
+    const int d = 32 >> step;
+#pragma unroll
+    for (int q = 0; q < (8 >> step); ++q) {
+      if (q * (2 << step) >= NV) continue;  // (zeros)
+      const double lo = t[2 * q], hi = t[2 * q + 1];
+      const bool up = lane & d;
+      t[q] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, d, 64);
+    }
+#pragma unroll
+    for (int q = 0; q < (8 >> step); ++q)
+      if (q * (2 << step) >= NV) t[q] = 0.0;
+  }
+  double r = t[0];
+  r += __shfl_xor(r, 2, 64);
+  r += __shfl_xor(r, 1, 64);
+  return r;
+}
+
 // Sum over a workgroup of NW wavefronts; result valid in every thread.
 template <int NW>
 __device__ __forceinline__ double block_sum_f64(double v, double* lds /* NW doubles */) {
