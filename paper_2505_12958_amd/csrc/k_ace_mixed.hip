@@ -1,7 +1,7 @@
 // ACE part of the AP force: bond basis (kernel 1), embedding and bond
 // gradients (kernel 3) of both precisions and the launchers of the three
-// phases; the rank kernels (phase 1) are in ace_rank.h / k_ace_rank.hip
-// (mixed) and k_ace_rank64.hip (FP64).
+// phases; the rank kernels (phase 1) are in k_ace_rank32.hip (mixed) and
+// k_ace_rank64.hip (FP64).
 #include "ace_basis.h"
 #include "ap_internal.h"
 #include "geom.h"
