@@ -1508,7 +1508,7 @@ ap_status ap_switching_update(ap_ctx* c, const ap_systems* sys, const double* po
     return st;
   const double full = (sw->n_csp / 2) * (2.0 * sys->cutoff) * (2.0 * sys->cutoff);
   PhaseTimer timer(ctx, AP_PHASE_BLEND, s);
-  AP_HIP(launch_switching(sv, pos, nl->nbr, nl->count, nl->capacity, (const int32_t*)ctx->cell_of.p,
+  AP_HIP(launch_switching(sv, pos, nl->nbr, nl->count, (const int32_t*)ctx->cell_of.p,
                           (const int32_t*)ctx->cell_start.p, (const int32_t*)ctx->cell_count.p,
                           (const int32_t*)ctx->cell_atoms.p, (const double4*)ctx->cell_pos.p, *sw, full,
                           (double*)ctx->sw_csp.p, (double*)ctx->sw_mu0.p,

@@ -389,7 +389,7 @@ hipError_t launch_lambda_grad(int32_t n, const double* pos, const ap_lambda_rule
                               double* force, double* vir_atom, hipStream_t s);
 // dynamic switching (k_switch.hip)
 hipError_t launch_switching(const SysView& sv, const double* pos, const int32_t* nbr,
-                            const int32_t* count, int32_t cap, const int32_t* cell_of,
+                            const int32_t* count, const int32_t* cell_of,
                             const int32_t* cell_start, const int32_t* cell_count,
                             const int32_t* cell_atoms, const double4* cell_pos,
                             const ap_switching& sw, double csp_full, double* csp, double* mu0,

@@ -63,6 +63,54 @@ __device__ __forceinline__ double wave_sums_f64(const double (&v)[NV], int lane)
   return r;
 }
 
+// Ascending sort of one value per lane over the wavefront: the bitonic network
+// on lane exchanges (DPP up to distance 8, row and half swaps beyond).
+template <int D>
+__device__ __forceinline__ void lane_pair(int v, int& lo, int& hi) {
+  int a = v, b;
+  if constexpr (D == 1) b = __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, true);        // quad_perm 1,0,3,2
+  else if constexpr (D == 2) b = __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xf, 0xf, true);   // quad_perm 2,3,0,1
+  else if constexpr (D == 4) {
+    b = __builtin_amdgcn_update_dpp(v, v, 0x1B, 0xf, 0xf, true);                            // quad_perm 3,2,1,0
+    b = __builtin_amdgcn_update_dpp(b, b, 0x141, 0xf, 0xf, true);                           // row_half_mirror
+  } else if constexpr (D == 8) b = __builtin_amdgcn_update_dpp(v, v, 0x128, 0xf, 0xf, true);  // row_ror 8
+  else {
+    const auto p = D == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)
+                           : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = (int)p[0];
+    b = (int)p[1];
+  }
+  lo = a < b ? a : b;
+  hi = a < b ? b : a;
+}
+
+// lanes that keep the smaller value of a pair at distance D in runs of S
+__host__ __device__ constexpr unsigned long long keep_low(int D, int S) {
+  unsigned long long m = 0;
+  for (int l = 0; l < 64; ++l)
+    if (((l & D) == 0) == ((l & S) == 0)) m |= 1ull << l;
+  return m;
+}
+
+template <int D, int S>
+__device__ __forceinline__ void sort_step(int& v) {
+  int lo, hi;
+  lane_pair<D>(v, lo, hi);
+  constexpr unsigned long long m = keep_low(D, S);
+  v = __builtin_amdgcn_inverse_ballot_w64(m) ? lo : hi;
+  if constexpr (D > 1) sort_step<D / 2, S>(v);
+}
+
+__device__ __forceinline__ int wave_sort(int v) {
+  sort_step<1, 2>(v);
+  sort_step<2, 4>(v);
+  sort_step<4, 8>(v);
+  sort_step<8, 16>(v);
+  sort_step<16, 32>(v);
+  sort_step<32, 64>(v);
+  return v;
+}
+
 // Sum over a workgroup of NW wavefronts; result valid in every thread.
 template <int NW>
 __device__ __forceinline__ double block_sum_f64(double v, double* lds /* NW doubles */) {
