@@ -401,7 +401,7 @@ __device__ __forceinline__ int row_slot(const int32_t* __restrict__ row, int c, 
 // atom and its neighbours) have no ACE term: zero, or unchanged when
 // accumulating.
 // Workgroups go to the XCDs in runs of 32, whose atoms share the neighbours'
-// rows in one L2 (390k atoms, all listed, 571 -> 490 us; runs of 8: 512 us).
+// rows in one L2 (370k atoms, all listed, 571 -> 490 us; runs of 8: 512 us).
 constexpr unsigned kGatherRun = 32;
 
 template <typename G, bool REV, bool VEC, int LN>
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(256) void k_ace_gather(int n, const int32_t* __rest
 // 21 us, 54k 119 -> 80 us, 108k 47 -> 22 us against 4 lanes and binary search).
 // Beyond, the loads themselves do: 8 lanes and the binary search, which reads
 // less (250k atoms 113 us, with 32 lanes 149 us, two-round search and 32 lanes
-// 142 us; 390k atoms, all listed, 725 us with 4 lanes, 568 us with 8,
+// 142 us; 370k atoms, all listed, 725 us with 4 lanes, 568 us with 8,
 // before the runs).
 constexpr int kGatherWide = 131072;
 

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_basis(
 
 // ---- kernel 3: embedding (FP64), bond gradients and virial, one wavefront per atom.
 // The neighbours come from the atom-major rows that kernel 1 wrote, and the nine
-// virial sums share their exchanges (250,000 atoms 104 -> 82 us; 390,000, all
+// virial sums share their exchanges (250,000 atoms 104 -> 82 us; 370,000, all
 // listed, 910 -> 812).
 // om_in: the two sets are n_buf * nA apart
 template <typename T, int NM, int LM, int KK>
