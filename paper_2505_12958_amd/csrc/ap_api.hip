@@ -1119,7 +1119,9 @@ ap_status ap_create(ap_ctx** out, int32_t device, int32_t precision, const ap_ea
     ctx->has_ace = true;
     setup_tuner(ctx, ace);
   }
-  if ((st = ensure(ctx, ctx->flags, 64)) != AP_OK) {
+  if ((st = ensure(ctx, ctx->flags, 64)) != AP_OK ||
+      hipHostMalloc((void**)&ctx->host_flag, 64, hipHostMallocDefault) != hipSuccess) {
+    if (st == AP_OK) st = fail(ctx, AP_ERR_HIP, "hipHostMalloc failed");
     g_create_err = ctx->err;
     ap_destroy((ap_ctx*)ctx);
     return st;
@@ -1148,6 +1150,7 @@ ap_status ap_destroy(ap_ctx* c) {
                     &ctx->sw_mu, &ctx->sw_flag, &ctx->sw_src, &ctx->sw_nsrc,
                     &ctx->e_eam_raw, &ctx->e_ace_raw, &ctx->nvt_ke, &ctx->nvt_sums, &ctx->nvt_fac})
     release(*b);
+  if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
   delete ctx;
   return AP_OK;
 }
@@ -1196,9 +1199,10 @@ ap_status ap_build_neighbors(ap_ctx* c, const ap_systems* sys, const double* pos
   if (nl->rev) AP_HIP(launch_rev((int32_t)N, nl->nbr, nl->count, nl->rev, s));
   ctx->cells_n_atoms = N;
   if (needed_capacity) {
-    int32_t need = 0;
-    AP_HIP(hipMemcpyAsync(&need, flags, 4, hipMemcpyDeviceToHost, s));
+    // into pinned memory: 20 us less than onto the stack (250 atoms 223 -> 200 us a call)
+    AP_HIP(hipMemcpyAsync(ctx->host_flag, flags, 4, hipMemcpyDeviceToHost, s));
     AP_HIP(hipStreamSynchronize(s));
+    const int32_t need = *ctx->host_flag;
     if (need > nl->capacity) {
       *needed_capacity = need;
       AP_HIP(launch_fill_i32(flags, 0, 1, s));

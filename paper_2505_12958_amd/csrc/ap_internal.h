@@ -286,6 +286,7 @@ struct Ctx {
   Buffer sw_csp, sw_mu0, sw_mu, sw_flag, sw_src, sw_nsrc;   // dynamic switching scratch
   Buffer e_eam_raw, e_ace_raw;          // unweighted per-atom energies of the last force calls
   int64_t cells_n_atoms = -1;           // atoms of the last neighbour build (its cell list)
+  int32_t* host_flag = nullptr;        // pinned: read-backs of the flags
   void* static_scratch = nullptr;      // this device's address of the static scratch array
   // launch mode of the mixed rank phase: forced (AP_RANK_MODE, >= 0) or tuned
   // per bucket of the atom count (timed on first use, optionally cached in
