@@ -143,7 +143,10 @@ __device__ __forceinline__ void sum_parts(double (&v)[NV], double* lds) {
 // the bond loop (same arithmetic as the general displacement).  kLds: the
 // pair tables are staged in LDS (dynamic shared memory sized by the host).
 // LN threads share an atom's bonds (thread part, part + LN, ...).  pos4: the
-// position and, in w, the atom's EAM weight 1 - lambda.
+// position and, in w, the atom's EAM weight 1 - lambda.  The closed form loads the
+// list entries of four bonds together (1.27 million atoms 336 -> 303 us); with
+// tables two bonds in flight are the better (2.66 million 630 us, batches of
+// two 669, of four 655).
 template <bool kOrtho, bool kLds, bool kAn, int LN>
 __global__ __launch_bounds__(256) void k_eam_density(SysView sv, TableDev rho_t, TableDev F_t,
                                                      EamAnalyticDev an,
@@ -157,7 +160,7 @@ __global__ __launch_bounds__(256) void k_eam_density(SysView sv, TableDev rho_t,
                              : stage_table(rho_t.c, rho_t.n - 1, tab_lds, kLds);
   if (kLds || kAn) __syncthreads();
   const int n = sv.n_atoms;
-  constexpr int kAtoms = 256 / LN;
+  constexpr int kAtoms = 256 / LN, kBatch = kAn ? 4 : 1;
   const int i = xcd_chunk(blockIdx.x, gridDim.x) * kAtoms + threadIdx.x % kAtoms, part = threadIdx.x / kAtoms;
   const bool live = i < n;
   const double4 pi = live ? pos4[i] : make_double4(0.0, 0.0, 0.0, 0.0);
@@ -170,20 +173,27 @@ __global__ __launch_bounds__(256) void k_eam_density(SysView sv, TableDev rho_t,
     const double* Hi = sv.Hi + 9 * s;
     const double Lx = H[0], Ly = H[4], Lz = H[8];
     const int c = count[i];
-#pragma unroll 2
-    for (int q = part; q < c; q += LN) {
-      const int j = nbr[(int64_t)q * n + i];
-      const double4 pj = pos4[j];
-      double dx, dy, dz;
-      if (kOrtho)
-        displacement_ortho(sv.per, Lx, Ly, Lz, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
-      else
-        displacement(ortho, H, Hi, sv.per, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
-      const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      double v, dv;
-      if constexpr (kAn) an_density(an, rho_c, r, v, dv);
-      else tab_eval(rho_t, rho_c, r, false, v, dv);
-      rho[0] += v;
+#pragma unroll (kAn ? 1 : 2)
+    for (int q = part; q < c; q += kBatch * LN) {
+      int js[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) js[u] = q + u * LN < c ? nbr[(int64_t)(q + u * LN) * n + i] : -1;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int j = js[u];
+        if (kBatch > 1 && j < 0) continue;
+        const double4 pj = pos4[j];
+        double dx, dy, dz;
+        if (kOrtho)
+          displacement_ortho(sv.per, Lx, Ly, Lz, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
+        else
+          displacement(ortho, H, Hi, sv.per, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
+        const double r = sqrt(dx * dx + dy * dy + dz * dz);
+        double v, dv;
+        if constexpr (kAn) an_density(an, rho_c, r, v, dv);
+        else tab_eval(rho_t, rho_c, r, false, v, dv);
+        rho[0] += v;
+      }
     }
   }
   sum_parts<LN>(rho, reinterpret_cast<double*>(tab_lds));
@@ -200,12 +210,13 @@ __global__ __launch_bounds__(256) void k_eam_density(SysView sv, TableDev rho_t,
   eF[i] = Fv;
 }
 
-// Waits on the gathered records: five wavefronts a SIMD and one bond at a time
-// hide them better than four with two bonds in flight (us: 250,000 atoms 107.7
-// -> 99.5, 1.27 million closed form 683 -> 616, 2.66 million 1390 -> 1265; six
-// wavefronts 103.5, 642, 1293).
+// Waits on the list entries and the gathered records.  The entries of four bonds
+// are loaded together, so their way from HBM is paid once for the four (us,
+// against a bond at a time with five wavefronts a SIMD: 1.27 million atoms closed
+// form 620 -> 589, 2.66 million 1265 -> 1157, 250,000 102 -> 98; five wavefronts
+// spill here: 600, 1265, 103; batches of eight 606, 2120, 179).
 template <bool kOrtho, bool kLds, bool kAn, int LN>
-__global__ __launch_bounds__(256, 5) void k_eam_force(SysView sv, TableDev rho_t, TableDev phi_t,
+__global__ __launch_bounds__(256, 4) void k_eam_force(SysView sv, TableDev rho_t, TableDev phi_t,
                                                    EamAnalyticDev an,
                                                    const double4* __restrict__ pos4,
                                                    const int32_t* __restrict__ nbr,
@@ -223,7 +234,7 @@ __global__ __launch_bounds__(256, 5) void k_eam_force(SysView sv, TableDev rho_t
                              : stage_table(phi_t.c, phi_t.n - 1, tab_lds + (rho_t.n - 1), kLds);
   if (kLds || kAn) __syncthreads();
   const int n = sv.n_atoms;
-  constexpr int kAtoms = 256 / LN;
+  constexpr int kAtoms = 256 / LN, kBatch = 4;
   const int k = xcd_chunk(blockIdx.x, gridDim.x) * kAtoms + threadIdx.x % kAtoms, part = threadIdx.x / kAtoms;
   const bool live = k < n;
   // force, pair energy and virial sums; atom k's bond gradients are parallel to
@@ -240,38 +251,45 @@ __global__ __launch_bounds__(256, 5) void k_eam_force(SysView sv, TableDev rho_t
     wk = pk.w;
     const double fk = wfp[k];
     const int c = count[k];
-    for (int q = part; q < c; q += LN) {
-      const int j = nbr[(int64_t)q * n + k];
-      const double4 pj = pos4[j];
-      const double wj = pj.w, fj = wfp[j];
-      if (wk == 0.0 && wj == 0.0) continue;
-      double dx, dy, dz;
-      if (kOrtho)
-        displacement_ortho(sv.per, Lx, Ly, Lz, pk.x, pk.y, pk.z, pj.x, pj.y, pj.z, dx, dy, dz);
-      else
-        displacement(ortho, H, Hi, sv.per, pk.x, pk.y, pk.z, pj.x, pj.y, pj.z, dx, dy, dz);
-      const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      const double ir = 1.0 / r;
-      double z, dzr, p, dp;
-      if constexpr (kAn) {
-        an_density(an, rho_c, r, z, dzr);
-        an_pair(an, phi_c, r, p, dp);
-      } else {
-        tab_eval(rho_t, rho_c, r, false, z, dzr);
-        tab_eval(phi_t, phi_c, r, false, p, dp);
-      }
-      const double a = ((fk + fj) * dzr + 0.5 * (wk + wj) * dp) * ir;
-      a10[0] += a * dx;
-      a10[1] += a * dy;
-      a10[2] += a * dz;
-      a10[3] += p;
-      // virial of atom k's own bond gradient G_kj = (w_k xi'_k zeta' + w_k Phi'/2) d/r
-      if (vir) {
-        const double g = (fk * dzr + 0.5 * wk * dp) * ir;
-        const double gx = g * dx, gy = g * dy, gz = g * dz;
-        a10[4] -= dx * gx; a10[5] -= dx * gy; a10[6] -= dx * gz;
-        a10[7] -= dy * gy; a10[8] -= dy * gz;
-        a10[9] -= dz * gz;
+    for (int q = part; q < c; q += kBatch * LN) {
+      int js[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) js[u] = q + u * LN < c ? nbr[(int64_t)(q + u * LN) * n + k] : -1;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int j = js[u];
+        if (kBatch > 1 && j < 0) continue;
+        const double4 pj = pos4[j];
+        const double wj = pj.w, fj = wfp[j];
+        if (wk == 0.0 && wj == 0.0) continue;
+        double dx, dy, dz;
+        if (kOrtho)
+          displacement_ortho(sv.per, Lx, Ly, Lz, pk.x, pk.y, pk.z, pj.x, pj.y, pj.z, dx, dy, dz);
+        else
+          displacement(ortho, H, Hi, sv.per, pk.x, pk.y, pk.z, pj.x, pj.y, pj.z, dx, dy, dz);
+        const double r = sqrt(dx * dx + dy * dy + dz * dz);
+        const double ir = 1.0 / r;
+        double z, dzr, p, dp;
+        if constexpr (kAn) {
+          an_density(an, rho_c, r, z, dzr);
+          an_pair(an, phi_c, r, p, dp);
+        } else {
+          tab_eval(rho_t, rho_c, r, false, z, dzr);
+          tab_eval(phi_t, phi_c, r, false, p, dp);
+        }
+        const double a = ((fk + fj) * dzr + 0.5 * (wk + wj) * dp) * ir;
+        a10[0] += a * dx;
+        a10[1] += a * dy;
+        a10[2] += a * dz;
+        a10[3] += p;
+        // virial of atom k's own bond gradient G_kj = (w_k xi'_k zeta' + w_k Phi'/2) d/r
+        if (vir) {
+          const double g = (fk * dzr + 0.5 * wk * dp) * ir;
+          const double gx = g * dx, gy = g * dy, gz = g * dz;
+          a10[4] -= dx * gx; a10[5] -= dx * gy; a10[6] -= dx * gz;
+          a10[7] -= dy * gy; a10[8] -= dy * gz;
+          a10[9] -= dz * gz;
+        }
       }
     }
   }
