@@ -338,9 +338,9 @@ def recorded_traffic(prec, ap, key):
         return None
     with open(rec) as f:
         d = json.load(f)
-    if "kernel_sources" not in d or "sources_sha256" not in d or d.get("key") != key:
+    if d.get("kernel_sources") != TRAFFIC_SOURCES or "sources_sha256" not in d or d.get("key") != key:
         return None
-    return d["traffic_bytes"] if sources_sha256(d["kernel_sources"]) == d["sources_sha256"] else None
+    return d["traffic_bytes"] if sources_sha256(TRAFFIC_SOURCES) == d["sources_sha256"] else None
 
 
 def describe(wl, mode, n_ace):
