@@ -8,11 +8,19 @@
 #include "scan.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ap {
 
 // ---- kernel 1: bond basis and atomic basis A, one wavefront per ACE atom
 constexpr int kBasisWaves = 4;
+// The number of listed atoms is on the device.  Up to kBondAtoms atoms every four
+// have a workgroup, which leaves at once beyond the list; beyond, kBondGrid
+// workgroups take the items in turn (kLoop).  An empty workgroup costs 0.2 ns:
+// 2.66 million atoms, 37,000 listed, kernel 1 and 3 240 + 259 -> 107 + 131 us;
+// the loop costs registers: 370,000 atoms, all listed, 506 + 824 -> 551 + 898 us.
+constexpr int kBondAtoms = 524288;
+constexpr int kBondGrid = 8192;
 
 // T: the arithmetic of the precision (float: mixed, double: FP64).  NM, LM,
 // KK > 0: model shape fixed at compile time (n_max, l_max, K), so
@@ -21,7 +29,7 @@ constexpr int kBasisWaves = 4;
 // offsets; NM = 0: the shape is read from the model at run time.  Items
 // item0 .. item0 + n_buf - 1 of the list; A_out and bn_out (mixed only) hold
 // these n_buf items.
-template <typename T, int NM, int LM, int KK>
+template <typename T, int NM, int LM, int KK, bool kLoop>
 __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_basis(
     SysView sv, BondDev<T> m, const double* __restrict__ pos, const double4* __restrict__ pos4,
     const int32_t* __restrict__ nbr, const int32_t* __restrict__ count, int cap,
@@ -42,9 +50,9 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_basis(
   T* RY = reinterpret_cast<T*>(lds) + wave * 64 * stride;
   const int n = sv.n_atoms;
   const int n_items = ace_list ? *n_ace_p : n_all;
-  const int local = blockIdx.x * kBasisWaves + wave;
+  const int n_local = min(n_buf, n_items - item0);
+  for (int local = blockIdx.x * kBasisWaves + wave; local < n_local; local += gridDim.x * kBasisWaves) {
   const int item = item0 + local;
-  if (local >= n_buf || item >= n_items) return;  // whole wavefront
   const int a = ace_list ? ace_list[item] : item;
   const int c = count[a];
   const int sy = sv.sys_of[a];
@@ -122,7 +130,11 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_basis(
     A_out[(int64_t)local * nA + e] = v;
     Asq[r] = v * v;
   }
-  if constexpr (sizeof(T) == 8) return;  // the FP64 rank kernels scale nothing
+  if constexpr (sizeof(T) == 8) {
+    if constexpr (!kLoop) return;
+    __syncwarp_ap();
+    continue;
+  }  // (the FP64 rank kernels scale nothing)
   // largest |A_(n,l)|^2 over the atom's single indices: it bounds every entry
   // of the coupled operand and fixes the atom's power-of-two scale there
   T* Q = RY + nB;
@@ -141,6 +153,9 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_basis(
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) bq = max(bq, __shfl_xor(bq, d, 64));
   if (lane == 0) bn_out[local] = (float)bq;
+  if constexpr (!kLoop) return;
+  __syncwarp_ap();  // the staging area is written again
+  }
 }
 
 // ---- kernel 3: embedding (FP64), bond gradients and virial, one wavefront per atom.
@@ -148,7 +163,7 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_basis(
 // virial sums share their exchanges (250,000 atoms 104 -> 82 us; 370,000, all
 // listed, 910 -> 812).
 // om_in: the two sets are n_buf * nA apart
-template <typename T, int NM, int LM, int KK>
+template <typename T, int NM, int LM, int KK, bool kLoop>
 __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_grad(
     SysView sv, BondDev<T> m, const double* __restrict__ pos, const double4* __restrict__ pos4,
     const int32_t* __restrict__ count, int cap, const double* __restrict__ lambda,
@@ -163,13 +178,13 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_grad(
   T* Om = om + m.apad;  // [nlm][K]
   const int n = sv.n_atoms;
   const int n_items = ace_list ? *n_ace_p : n_all;
-  const int local = blockIdx.x * kBasisWaves + wave;
-  const int item = item0 + local;
-  if (local >= n_buf || item >= n_items) return;  // whole wavefront
+  const int n_local = min(n_buf, n_items - item0);
   const int64_t plane = (int64_t)n_buf * m.nA;
   auto om_at = [&](int64_t o, int p) {
     return (double)om_in[o + p * plane];
   };
+  for (int local = blockIdx.x * kBasisWaves + wave; local < n_local; local += gridDim.x * kBasisWaves) {
+  const int item = item0 + local;
   const int a = ace_list ? ace_list[item] : item;
   const double lam = lambda ? lambda[a] : 1.0;
   // phi_p = X.Z/2 summed over L.  X rows are homogeneous in A of degree 2
@@ -264,10 +279,13 @@ __global__ __launch_bounds__(64 * kBasisWaves) void k_ace_grad(
     e_atom[a] += lam * E;
     if (e_raw) e_raw[a] = E;
   }
+  if constexpr (!kLoop) return;
+  __syncwarp_ap();  // om and Om are written again
+  }
 }
 
 // kernels 1 and 3 of one precision over the items item0 .. item0 + n_buf - 1
-// (grids are sized for all of them; wavefronts past *n_ace leave at once)
+// (wavefronts past *n_ace leave at once, or take every so many items up to it)
 template <typename T>
 static hipError_t launch_bonds(const BondDev<T>& m, const SysView& sv, const BondArgs& b, int phase,
                                int item0, int n_buf, T* pair_g, T* A_buf, T* om_buf, T* phi_buf,
@@ -275,7 +293,9 @@ static hipError_t launch_bonds(const BondDev<T>& m, const SysView& sv, const Bon
   const int items = std::min(n_buf, b.n_atoms - item0);
   if (items <= 0) return hipSuccess;
   const int nlm = (m.l_max + 1) * (m.l_max + 1);
-  const dim3 grid((items + kBasisWaves - 1) / kBasisWaves), block(64 * kBasisWaves);
+  const bool loop = b.n_atoms > kBondAtoms;
+  const int groups = (items + kBasisWaves - 1) / kBasisWaves;
+  const dim3 grid(loop ? std::min(groups, kBondGrid) : groups), block(64 * kBasisWaves);
   const size_t lds = kBasisWaves * sizeof(T) *
                      (phase == 0 ? (size_t)64 * (m.K + nlm) : (size_t)(m.apad + kMaxLM * kMaxK));
   auto attr = [&](auto kern) {
@@ -301,11 +321,15 @@ static hipError_t launch_bonds(const BondDev<T>& m, const SysView& sv, const Bon
   };
   const bool w844 = m.n_max == 8 && m.l_max == 4 && m.K == 8;
   const bool s633 = m.n_max == 6 && m.l_max == 3 && m.K == 6;
-  if (phase == 0)
-    return w844 ? basis(k_ace_basis<T, 8, 4, 8>)
-                : s633 ? basis(k_ace_basis<T, 6, 3, 6>) : basis(k_ace_basis<T, 0, 0, 0>);
-  return w844 ? grad(k_ace_grad<T, 8, 4, 8>)
-              : s633 ? grad(k_ace_grad<T, 6, 3, 6>) : grad(k_ace_grad<T, 0, 0, 0>);
+  auto run = [&](auto lp) {
+    constexpr bool kLoop = decltype(lp)::value;
+    if (phase == 0)
+      return w844 ? basis(k_ace_basis<T, 8, 4, 8, kLoop>)
+                  : s633 ? basis(k_ace_basis<T, 6, 3, 6, kLoop>) : basis(k_ace_basis<T, 0, 0, 0, kLoop>);
+    return w844 ? grad(k_ace_grad<T, 8, 4, 8, kLoop>)
+                : s633 ? grad(k_ace_grad<T, 6, 3, 6, kLoop>) : grad(k_ace_grad<T, 0, 0, 0, kLoop>);
+  };
+  return loop ? run(std::true_type{}) : run(std::false_type{});
 }
 
 hipError_t launch_ace_bonds64(const Ctx& c, const SysView& sv, const BondArgs& b, int phase, int item0,
