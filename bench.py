@@ -297,7 +297,7 @@ def record_traffic(fetch_csv, write_csv, key_json, out):
         for r in csv.DictReader(open(path)):
             if r["Counter_Name"] != counter:
                 continue
-            name = re.sub(r"\(.*", "", r["Kernel_Name"])
+            name = re.sub(r"\(.*", "", r["Kernel_Name"].replace("(anonymous namespace)::", ""))
             a = acc.setdefault(name, {})
             a[r["Dispatch_Id"]] = a.get(r["Dispatch_Id"], 0.0) + float(r["Counter_Value"])
         return {k: sum(v.values()) / len(v) for k, v in acc.items()}
@@ -311,6 +311,8 @@ def record_traffic(fetch_csv, write_csv, key_json, out):
     f_scale = COPY_BYTES / (fetch[calib[0]] * 1024.0)
     w_scale = COPY_BYTES / (write[calib[0]] * 1024.0)
     ranks = sorted(k for k in fetch if re.search(r"k_ace_rank32<", k))
+    if not ranks:
+        raise SystemExit("no rank kernel in the counter file")
     fb = sum(fetch[k] for k in ranks) * 1024.0 * f_scale
     wb = sum(write.get(k, 0.0) for k in ranks) * 1024.0 * w_scale
     with open(key_json) as f:
