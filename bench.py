@@ -446,10 +446,13 @@ def main():
     roof_ph = roofline_model(ctx, ap, wl, n_ace, n_bonds, n_bonds_ace, fp64)
     t_roof_step = sum(roof_ph.values())
     if fp64:
-        flops = ctx.info("ace.flops_atom") * n_ace + ctx.info("ace.flops_bond") * n_bonds_ace
+        # the rank kernels (the bond kernels are a phase of their own); a step
+        # runs them batch after batch
+        t_rank = ace_ms / steps_prof * 1e-3
+        flops = ctx.info("ace.flops_atom") * n_ace
         achieved = flops / t_rank / 1e12
         roof = {"bound": "alu", "achieved": achieved, "peak": PEAK["fp64_valu"], "unit": "TFLOP/s",
-                "frac": achieved / PEAK["fp64_valu"], "traffic": None, "kernel": "k_ace_fp64",
+                "frac": achieved / PEAK["fp64_valu"], "traffic": None, "kernel": "k_ace_rank64<L>, L=0..8",
                 "kernel_avg_ms": t_rank * 1e3, "flops_per_launch": flops}
     else:
         f_valu = (ctx.info("ace.flops_atom") - ctx.info("ace.flops_contract")) * n_ace
