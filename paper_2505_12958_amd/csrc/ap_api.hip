@@ -614,7 +614,51 @@ static ap_status fold_rank32(Ctx* ctx, const ChanMap& chan, const std::vector<Co
       mfma += 2 * 3.0 * 2.0 * 16 * 16 * 32 * ct * ns / kMT32;
       row_tiles.push_back(Unit{row, 0, s0, ns});
     }
-    // units, adjoint jobs and LDS layout of the two variants
+    // adjoint jobs (the same for both sets), largest first, dealt to the wide
+    // variant's wavefronts.  The jobs of one target l on one wavefront form a
+    // group, which has a gradient slot of its own and is added up job by job;
+    // the slots are added in order.  The narrow variant deals these groups
+    // whole, so both add the same terms in the same order and which of them the
+    // tuner picks leaves no trace in the results.
+    struct Job { int lt, lp, k; double cost; };
+    struct Group { double cost; std::vector<int4> jobs; };
+    std::vector<Job> js;
+    for (int lt = 0; lt <= a.l_max; ++lt)
+      for (int lp = 0; lp <= a.l_max; ++lp) {
+        if (!(std::abs(lt - lp) <= L && L <= lt + lp && ((lt + lp + L) & 1) == 0)) continue;
+        bool any = false;
+        for (int na = 0; na < a.n_max && !any; ++na)
+          for (int nb = 0; nb < a.n_max && !any; ++nb)
+            any = rowtab[((size_t)L * nidx + na * lp1 + lt) * nidx + nb * lp1 + lp] >= 0;
+        if (!any) continue;
+        const int w2 = 2 * lp + 1, nc = rank32_chunks(lp, L);
+        for (int k = 0; k < nc; ++k) {
+          const int mc = (k + 1) * w / nc - k * w / nc;
+          js.push_back({lt, lp, k, a.n_max * (w2 * mc + 1.0 * (w2 + mc) + 12) + 2.0 * w2 * mc + 60});
+        }
+      }
+    std::stable_sort(js.begin(), js.end(), [](const Job& p, const Job& q) { return p.cost > q.cost; });
+    const int nww = rank32_waves(L);
+    std::vector<std::vector<int4>> wide_jobs(nww);
+    std::vector<double> wide_load(nww, 0.0);
+    std::vector<std::vector<int>> slot(nww, std::vector<int>(lp1, -1));
+    std::vector<Group> groups(kSlots32 * lp1, Group{0.0, {}});
+    for (auto& j : js) {
+      int best = -1;
+      for (int wv = 0; wv < nww; ++wv)
+        if ((slot[wv][j.lt] >= 0 || P.nslots[j.lt] < kSlots32) && (best < 0 || wide_load[wv] < wide_load[best])) best = wv;
+      const bool first = slot[best][j.lt] < 0;
+      if (first) slot[best][j.lt] = P.nslots[j.lt]++;
+      const int sl = slot[best][j.lt];
+      wide_jobs[best].push_back(make_int4((j.lt * 5 + j.lp) * 8 + j.k, sl, first ? 1 : 0, j.lt));
+      wide_load[best] += j.cost;
+      groups[j.lt * kSlots32 + sl].jobs.push_back(wide_jobs[best].back());
+      groups[j.lt * kSlots32 + sl].cost += j.cost;
+    }
+    std::stable_sort(groups.begin(), groups.end(), [](const Group& p, const Group& q) { return p.cost > q.cost; });
+    P.slots = 1;
+    for (int l = 0; l < lp1; ++l) P.slots = std::max(P.slots, P.nslots[l]);
+    // units, dealing of the adjoint jobs and LDS layout of the two variants
     for (int v = 0; v < 2; ++v) {
       if (v == 1 && !narrow) {
         ctx->r32_lv[1][L] = ctx->r32_lv[0][L];
@@ -622,7 +666,6 @@ static ap_status fold_rank32(Ctx* ctx, const ChanMap& chan, const std::vector<Co
         continue;
       }
       P.small = v == 0 && narrow;
-      for (int l = 0; l < lp1; ++l) P.nslots[l] = 0;
       std::vector<Unit> us = row_tiles;
       if (!P.small && rank32_sets(L) == 1)
         for (auto& u : row_tiles) us.push_back(Unit{u.row, 1, u.s0, u.ns});
@@ -646,36 +689,15 @@ static ap_status fold_rank32(Ctx* ctx, const ChanMap& chan, const std::vector<Co
         for (int u = 0; u < P.nu; ++u)
           units.push_back(u < (int)p.size() ? make_int4(p[u].row, p[u].set, p[u].s0, p[u].ns)
                                             : make_int4(-1, 0, 0, 0));
-      // adjoint jobs (the same for both sets), largest first
-      struct Job { int lt, lp, k; double cost; };
-      std::vector<Job> js;
-      for (int lt = 0; lt <= a.l_max; ++lt)
-        for (int lp = 0; lp <= a.l_max; ++lp) {
-          if (!(std::abs(lt - lp) <= L && L <= lt + lp && ((lt + lp + L) & 1) == 0)) continue;
-          bool any = false;
-          for (int na = 0; na < a.n_max && !any; ++na)
-            for (int nb = 0; nb < a.n_max && !any; ++nb)
-              any = rowtab[((size_t)L * nidx + na * lp1 + lt) * nidx + nb * lp1 + lp] >= 0;
-          if (!any) continue;
-          const int w2 = 2 * lp + 1, nc = rank32_chunks(lp, L);
-          for (int k = 0; k < nc; ++k) {
-            const int mc = (k + 1) * w / nc - k * w / nc;
-            js.push_back({lt, lp, k, a.n_max * (w2 * mc + 1.0 * (w2 + mc) + 12) + 2.0 * w2 * mc + 60});
-          }
+      // adjoint jobs: the groups, largest first, onto the least loaded wavefront
+      std::vector<std::vector<int4>> pj = P.small ? std::vector<std::vector<int4>>(nw) : wide_jobs;
+      std::vector<double> jl = P.small ? std::vector<double>(nw, 0.0) : wide_load;
+      if (P.small)
+        for (auto& g : groups) {
+          const size_t best = std::min_element(jl.begin(), jl.end()) - jl.begin();
+          pj[best].insert(pj[best].end(), g.jobs.begin(), g.jobs.end());
+          jl[best] += g.cost;
         }
-      std::stable_sort(js.begin(), js.end(), [](const Job& p, const Job& q) { return p.cost > q.cost; });
-      std::vector<std::vector<int4>> pj(nw);
-      std::vector<double> jl(nw, 0.0);
-      std::vector<std::vector<int>> slot(nw, std::vector<int>(lp1, -1));
-      for (auto& j : js) {
-        int best = -1;
-        for (int wv = 0; wv < nw; ++wv)
-          if ((slot[wv][j.lt] >= 0 || P.nslots[j.lt] < kSlots32) && (best < 0 || jl[wv] < jl[best])) best = wv;
-        const bool first = slot[best][j.lt] < 0;
-        if (first) slot[best][j.lt] = P.nslots[j.lt]++;
-        pj[best].push_back(make_int4((j.lt * 5 + j.lp) * 8 + j.k, slot[best][j.lt], first ? 1 : 0, j.lt));
-        jl[best] += j.cost;
-      }
       P.job0 = (int32_t)job_ptr.size();
       for (auto& p : pj) {
         job_ptr.push_back((int32_t)jobs.size());
@@ -683,8 +705,6 @@ static ap_status fold_rank32(Ctx* ctx, const ChanMap& chan, const std::vector<Co
       }
       job_ptr.push_back((int32_t)jobs.size());
       P.phi_wave = (int32_t)(std::min_element(jl.begin(), jl.end()) - jl.begin());
-      P.slots = 1;
-      for (int l = 0; l < lp1; ++l) P.slots = std::max(P.slots, P.nslots[l]);
       // LDS: A, slots, scales, channel groups, channel rows (and one spare row), X / Z
       P.sx_off = (int32_t)(4 * (size_t)kMT32 * x.apad * (1 + P.slots));
       P.rs_off = P.sx_off + 4 * kMT32;
