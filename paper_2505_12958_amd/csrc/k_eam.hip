@@ -45,17 +45,19 @@ __device__ __forceinline__ void tab_eval(const TableDev& t, const double4* coef,
 // the vector units busy (511 instructions per bond of the force pass); the
 // interval search is one compare and one add per knot.  Against extended
 // precision the W pair function's error falls from 1.2e-14 (its knots cancel)
-// to 6e-17, the density's from 9e-17 to 7e-17.
+// to 6e-17, the density's from 9e-17 to 7e-17.  An r that is infinite or not a
+// number lies beyond every knot and gives zero, as in the sum.
 __device__ __forceinline__ void an_knots(const KnotDev& d, const double4* coef, double r, double& v,
                                          double& dv) {
   int k = 0;
   for (int i = 0; i < d.n4; i += 4) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) k += d.knot[i + q] < r ? 1 : 0;  // padded with +inf
+    for (int q = 0; q < 4; ++q) k += !(d.knot[i + q] >= r) ? 1 : 0;  // padded with +inf
   }
+  k = min(k, d.n);
   const double4 c = coef[k];
-  // (beyond the last knot the coefficients are zero)
-  const double t = reinterpret_cast<const double*>(coef + d.n + 1)[k] - r;
+  // (beyond the last knot the coefficients are zero, and so is t)
+  const double t = fmax(reinterpret_cast<const double*>(coef + d.n + 1)[k] - r, 0.0);
   v = c.x + t * (c.y + t * (c.z + t * c.w));
   dv = -(c.y + t * (2.0 * c.z + t * 3.0 * c.w));
 }
@@ -73,7 +75,7 @@ __device__ __forceinline__ void an_density(const EamAnalyticDev& p, const double
 // Phi^Fit(r): screened Coulomb below r_lo, quintic bridge up to r_hi, knot sum above
 __device__ __forceinline__ void an_pair(const EamAnalyticDev& p, const double4* coef, double r, double& v,
                                         double& dv) {
-  if (r > p.r_hi) {
+  if (!(r <= p.r_hi)) {
     an_knots(p.phi, coef, r, v, dv);
   } else if (r < p.r_lo) {
     const double x = r / p.a_zbl;
