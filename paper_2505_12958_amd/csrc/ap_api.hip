@@ -960,8 +960,12 @@ static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
 // against 132 us), the narrow one the higher throughput (389,694 atoms 3.4
 // against 4.0 ms).  Models without such ranks have mode 0 only.
 // AP_RANK_MODE=0/1/2 forces a mode; AP_AUTOTUNE=0 turns the tuner off (mode 1);
-// AP_AUTOTUNE_CACHE names a JSON file {"<device>|<model shape>|b<bucket>": mode,
-// ...} that is read when a context is created and updated after each tuning.
+// AP_AUTOTUNE_CACHE names a JSON file {"<device>|<version>|<model shape>|b<bucket>":
+// mode, ...} that is read when a context is created and updated after each
+// tuning.  The version stands for the variants the modes number: a choice made
+// among others (keys without one: the launch forms of former kernels, whose 0
+// and 1 mean something else) is left in the file and ignored.
+constexpr const char* kTuneVersion = "variants 1";
 static int size_bucket(int64_t n) {
   int b = 0;
   while ((int64_t(1) << (b + 1)) <= std::max<int64_t>(n, 1)) ++b;
@@ -1005,7 +1009,7 @@ static void setup_tuner(Ctx* ctx, const ap_ace_model* m) {
   std::string dev = "hip";
   if (hipGetDeviceProperties(&prop, ctx->device) == hipSuccess) dev = std::string(prop.gcnArchName) + " " + prop.name;
   std::ostringstream k;
-  k << dev << "|ace " << m->n_max << " " << m->l_max << " " << m->K << " " << m->nu_max << " "
+  k << dev << "|" << kTuneVersion << "|ace " << m->n_max << " " << m->l_max << " " << m->K << " " << m->nu_max << " "
     << ctx->ace.L_max << " " << m->n_funcs;
   ctx->tune_key = k.str();
   if (const char* f = std::getenv("AP_RANK_MODE")) {

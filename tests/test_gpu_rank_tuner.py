@@ -1,0 +1,70 @@
+"""The choice between the narrow and the wide variant of the mixed rank kernels:
+what the cache file fixes, and when the library measures at all."""
+import json
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2505_12958_amd import ap
+from paper_2505_12958_amd import workloads as w
+
+pytestmark = pytest.mark.gpu
+
+
+class Ace:
+    """ACE forces of a crystal, every atom listed or none."""
+
+    def __init__(self, ncell, n_max, l_max, nu):
+        wl = self.wl = w.make_bulk("edge", ncell, w.A_W, 3, n_max=n_max, l_max=l_max, nu_max=nu, r_full=4.0)
+        n, f64 = wl.n_atoms, dict(dtype=torch.float64, device="cuda")
+        self.S = ap.SystemsArg.from_workload(wl)
+        self.pos = torch.tensor(np.ascontiguousarray(wl.pos.T), **f64)
+        self.nl = ap.NeighbourList(n, 64)
+        self.lam, self.e, self.F = torch.ones(n, **f64), torch.zeros(n, **f64), torch.zeros((3, n), **f64)
+        self.list = torch.arange(n, dtype=torch.int32, device="cuda")
+        self.n_all = torch.tensor([n], dtype=torch.int32, device="cuda")
+        self.n_none = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+    def neighbours(self, ctx):
+        ctx.build_neighbors(self.S, self.pos, self.nl)
+
+    def forces(self, ctx, n_ace=None):
+        ctx.ace_forces(self.S, self.pos, self.nl, self.lam, self.list, self.n_all if n_ace is None else n_ace,
+                       self.e, self.F)
+
+    def run(self, n_ace=None):
+        """One call on a new context: the variant it took."""
+        ctx = ap.Context(None, self.wl.ace, ap.AP_PREC_MIXED)
+        self.neighbours(ctx)
+        self.forces(ctx, n_ace)
+        torch.cuda.synchronize()
+        mode = int(ctx.info("ace.rank_mode"))
+        ctx.close()
+        return mode
+
+
+@pytest.fixture
+def cache(tmp_path, monkeypatch):
+    monkeypatch.delenv("AP_RANK_MODE", raising=False)
+    monkeypatch.delenv("AP_AUTOTUNE", raising=False)
+    monkeypatch.setenv("AP_AUTOTUNE_CACHE", str(tmp_path / "tune.json"))
+    return tmp_path / "tune.json"
+
+
+def test_a_cached_choice_is_taken_unless_it_is_of_the_earlier_kernels(cache):
+    case = Ace(4, 3, 2, 3)
+    mode = case.run()
+    (key, val), = json.loads(cache.read_text()).items()
+    assert val == mode and mode in (0, 1)
+    for planted in (0, 1):
+        cache.write_text(json.dumps({key: planted}))
+        assert case.run() == planted
+        assert json.loads(cache.read_text()) == {key: planted}
+    # a key without the version is of kernels that are gone: ignored, and kept
+    dev, version, rest = key.split("|", 2)
+    assert rest.startswith("ace 3 2 3 3 ")
+    cache.write_text(json.dumps({f"{dev}|{rest}": 1}))
+    case.run()
+    entries = json.loads(cache.read_text())
+    assert set(entries) == {key, f"{dev}|{rest}"}
