@@ -958,7 +958,8 @@ static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
 // faster is kept: the wide one has the shorter way through a single tile (250
 // ACE atoms of the (6, 3, nu <= 3) model 50 against 66 us, 7,849 atoms 126
 // against 132 us), the narrow one the higher throughput (389,694 atoms 3.4
-// against 4.0 ms).  Models without such ranks have mode 0 only.
+// against 4.0 ms).  Models without such ranks have mode 0 only and are not
+// timed: their calls never wait for the stream.
 // AP_RANK_MODE=0/1/2 forces a mode; AP_AUTOTUNE=0 turns the tuner off (mode 1);
 // AP_AUTOTUNE_CACHE names a JSON file {"<device>|<version>|<model shape>|b<bucket>":
 // mode, ...} that is read when a context is created and updated after each
@@ -1424,29 +1425,32 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
       if (it != ctx->rank_mode_tuned.end()) {
         mode = it->second;
       } else {
-        // time every mode twice on these inputs (the first round warms up);
-        // each run rewrites the phase's outputs completely
-        // (small models have two)
-        const int n_modes = ctx->rank_narrow ? 2 : 1;
-        hipEvent_t ev[2 * AP_RANK_N_MODES];
-        for (auto& e : ev) AP_HIP(hipEventCreate(&e));
-        for (int rep = 0; rep < 2; ++rep)
+        if (!ctx->rank_narrow) {
+          mode = AP_RANK_NARROW;  // no choice: nothing to time, nothing to wait for
+        } else {
+          // time both modes twice on these inputs (the first round warms up);
+          // each run rewrites the phase's outputs completely
+          constexpr int n_modes = 2;
+          hipEvent_t ev[2 * n_modes];
+          for (auto& e : ev) AP_HIP(hipEventCreate(&e));
+          for (int rep = 0; rep < 2; ++rep)
+            for (int md = 0; md < n_modes; ++md) {
+              if (rep == 1) AP_HIP(hipEventRecord(ev[2 * md], s));
+              AP_HIP(phase_run(1, md));
+              if (rep == 1) AP_HIP(hipEventRecord(ev[2 * md + 1], s));
+            }
+          AP_HIP(hipEventSynchronize(ev[2 * n_modes - 1]));
+          float best = 0.f;
           for (int md = 0; md < n_modes; ++md) {
-            if (rep == 1) AP_HIP(hipEventRecord(ev[2 * md], s));
-            AP_HIP(phase_run(1, md));
-            if (rep == 1) AP_HIP(hipEventRecord(ev[2 * md + 1], s));
+            float ms = 0.f;
+            AP_HIP(hipEventElapsedTime(&ms, ev[2 * md], ev[2 * md + 1]));
+            if (mode < 0 || ms < best) {
+              best = ms;
+              mode = md;
+            }
           }
-        AP_HIP(hipEventSynchronize(ev[2 * n_modes - 1]));
-        float best = 0.f;
-        for (int md = 0; md < n_modes; ++md) {
-          float ms = 0.f;
-          AP_HIP(hipEventElapsedTime(&ms, ev[2 * md], ev[2 * md + 1]));
-          if (mode < 0 || ms < best) {
-            best = ms;
-            mode = md;
-          }
+          for (auto& e : ev) (void)hipEventDestroy(e);
         }
-        for (auto& e : ev) (void)hipEventDestroy(e);
         ctx->rank_mode_tuned[bucket] = mode;
         if (!ctx->tune_cache.empty())
           write_tune_cache(ctx->tune_cache, ctx->tune_key + "|b" + std::to_string(bucket), mode);

@@ -68,3 +68,29 @@ def test_a_cached_choice_is_taken_unless_it_is_of_the_earlier_kernels(cache):
     case.run()
     entries = json.loads(cache.read_text())
     assert set(entries) == {key, f"{dev}|{rest}"}
+
+
+def test_a_model_with_one_variant_is_not_timed(cache):
+    """(8, 4): too many components for a narrow variant.  The first call of a size
+    bucket only enqueues: an event behind a long kernel is still pending after it."""
+    big, small = Ace(6, 8, 4, 2), Ace(4, 8, 4, 2)
+    ctx = ap.Context(None, big.wl.ace, ap.AP_PREC_MIXED)
+    big.neighbours(ctx)
+    big.forces(ctx)  # sizes the buffers
+    small.neighbours(ctx)
+    assert big.wl.n_atoms.bit_length() != small.wl.n_atoms.bit_length()
+    torch.cuda.synchronize()
+    t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    t[0].record()
+    torch.cuda._sleep(1_000_000)
+    t[1].record()
+    torch.cuda.synchronize()
+    cycles = int(1_000_000 * 300.0 / t[0].elapsed_time(t[1]))  # 0.3 s
+    behind = torch.cuda.Event()
+    torch.cuda._sleep(cycles)
+    behind.record()
+    small.forces(ctx)
+    pending = not behind.query()
+    torch.cuda.synchronize()
+    assert pending and int(ctx.info("ace.rank_mode")) == 0
+    ctx.close()
