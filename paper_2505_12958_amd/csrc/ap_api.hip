@@ -960,6 +960,11 @@ static ap_status fold_ace(Ctx* ctx, const ap_ace_model* m) {
 // against 132 us), the narrow one the higher throughput (389,694 atoms 3.4
 // against 4.0 ms).  Models without such ranks have mode 0 only and are not
 // timed: their calls never wait for the stream.
+// The bucket is that of all atoms, since the list's length is on the device; a
+// choice made on a list that gives some CU no tile, and is not all atoms, says
+// little about a longer one (dynamic switching starts with an empty list).  It
+// holds for the calls that follow, but is made again at call 64, 4096, ... of
+// the bucket (not under stream capture) and isn't written to the file.
 // AP_RANK_MODE=0/1/2 forces a mode; AP_AUTOTUNE=0 turns the tuner off (mode 1);
 // AP_AUTOTUNE_CACHE names a JSON file {"<device>|<version>|<model shape>|b<bucket>":
 // mode, ...} that is read when a context is created and updated after each
@@ -1024,7 +1029,7 @@ static void setup_tuner(Ctx* ctx, const ap_ace_model* m) {
     const std::string pre = ctx->tune_key + "|b";
     for (auto& kv : read_tune_cache(ctx->tune_cache))
       if (kv.first.compare(0, pre.size(), pre) == 0 && kv.second >= 0 && kv.second < AP_RANK_N_MODES)
-        ctx->rank_mode_tuned[std::atoi(kv.first.c_str() + pre.size())] = kv.second;
+        ctx->rank_choice[std::atoi(kv.first.c_str() + pre.size())] = RankChoice{kv.second, true};
   }
 }
 
@@ -1421,16 +1426,24 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
     if (mode > AP_RANK_NARROW && !ctx->rank_narrow) mode = AP_RANK_NARROW;
     if (mode < 0) {
       const int bucket = size_bucket(N);
-      auto it = ctx->rank_mode_tuned.find(bucket);
-      if (it != ctx->rank_mode_tuned.end()) {
-        mode = it->second;
-      } else {
-        if (!ctx->rank_narrow) {
-          mode = AP_RANK_NARROW;  // no choice: nothing to time, nothing to wait for
-        } else {
+      RankChoice& ch = ctx->rank_choice[bucket];
+      bool settle = false;
+      if (!ctx->rank_narrow) {
+        // no choice: nothing to time, nothing to wait for
+        settle = !ch.settled;
+        ch.mode = AP_RANK_NARROW;
+      } else if (!ch.settled && ch.calls++ >= ch.next) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (ch.mode >= 0) AP_HIP(hipStreamIsCapturing(s, &cap));
+        if (cap == hipStreamCaptureStatusNone) {
           // time both modes twice on these inputs (the first round warms up);
           // each run rewrites the phase's outputs completely
           constexpr int n_modes = 2;
+          int n_cu = 256;
+          AP_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
+          int32_t* listed = ctx->host_flag + 1;
+          *listed = (int32_t)N;
+          if (ace_list) AP_HIP(hipMemcpyAsync(listed, n_ace, 4, hipMemcpyDeviceToHost, s));
           hipEvent_t ev[2 * n_modes];
           for (auto& e : ev) AP_HIP(hipEventCreate(&e));
           for (int rep = 0; rep < 2; ++rep)
@@ -1444,17 +1457,22 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
           for (int md = 0; md < n_modes; ++md) {
             float ms = 0.f;
             AP_HIP(hipEventElapsedTime(&ms, ev[2 * md], ev[2 * md + 1]));
-            if (mode < 0 || ms < best) {
+            if (md == 0 || ms < best) {
               best = ms;
-              mode = md;
+              ch.mode = md;
             }
           }
           for (auto& e : ev) (void)hipEventDestroy(e);
+          settle = *listed >= std::min<int64_t>(N, (int64_t)kMT32 * n_cu);
+          ch.next = ch.next ? 64 * ch.next : 64;
         }
-        ctx->rank_mode_tuned[bucket] = mode;
-        if (!ctx->tune_cache.empty())
-          write_tune_cache(ctx->tune_cache, ctx->tune_key + "|b" + std::to_string(bucket), mode);
       }
+      if (settle) {
+        ch.settled = true;
+        if (!ctx->tune_cache.empty())
+          write_tune_cache(ctx->tune_cache, ctx->tune_key + "|b" + std::to_string(bucket), ch.mode);
+      }
+      mode = ch.mode;
     }
     ctx->last_rank_mode = mode;
     {

@@ -249,6 +249,13 @@ struct SysCache {
   Buffer chunk_lo_d, chunk_hi_d, sys_chunk_d;  // reduction chunks
 };
 
+// the mixed rank phase's mode for a bucket of the atom count
+struct RankChoice {
+  int mode = -1;
+  bool settled = false;         // measured on a list that stands for the bucket, or read from the file
+  int64_t calls = 0, next = 0;  // until then: calls so far, the call that measures again
+};
+
 struct Ctx {
   int device = 0;
   int precision = AP_PREC_FP64;
@@ -292,7 +299,7 @@ struct Ctx {
   // per bucket of the atom count (timed on first use, optionally cached in
   // the JSON file named by AP_AUTOTUNE_CACHE)
   int rank_mode_forced = -1;
-  std::map<int, int> rank_mode_tuned;
+  std::map<int, RankChoice> rank_choice;
   std::string tune_key;                 // device and model shape, prefix of the cache keys
   std::string tune_cache;               // cache file path ("" = none)
   int last_rank_mode = -1;

@@ -94,3 +94,19 @@ def test_a_model_with_one_variant_is_not_timed(cache):
     torch.cuda.synchronize()
     assert pending and int(ctx.info("ace.rank_mode")) == 0
     ctx.close()
+
+
+def test_a_choice_on_an_empty_list_is_not_final(cache):
+    case = Ace(4, 3, 2, 3)
+    ctx = ap.Context(None, case.wl.ace, ap.AP_PREC_MIXED)
+    case.neighbours(ctx)
+    case.forces(ctx, case.n_none)
+    assert not cache.exists()
+    for _ in range(63):
+        case.forces(ctx)
+    assert not cache.exists()
+    case.forces(ctx)  # call 64 measures again, now with every atom listed
+    mode = int(ctx.info("ace.rank_mode"))
+    (val,) = json.loads(cache.read_text()).values()
+    assert val == mode and mode in (0, 1)
+    ctx.close()
