@@ -45,8 +45,8 @@
  *
  * Determinism: no floating-point atomics in either precision; forces are
  * gathered with a reverse-slot index and every sum has a fixed order (the
- * mixed path's partial phi sums of a rank are added slot by slot), so results
- * are bitwise reproducible run to run.  Integer atomics (work queues, cell
+ * rank kernels' partial gradients are added slot by slot, in one order in every
+ * variant), so results are bitwise reproducible run to run.  Integer atomics (work queues, cell
  * counts, overflow maxima, the switching spread's maximum over FP64 bit
  * patterns of non-negative values) do not affect results.
  */
@@ -401,8 +401,9 @@ ap_status ap_step(ap_ctx* ctx, const ap_systems* sys, ap_md_state* st, int32_t n
 ap_status ap_check(ap_ctx* ctx, void* stream);
 
 /* Per-phase GPU timing with HIP events recorded on each call's stream around
- * the kernels of a phase (AP_PHASE_ACE brackets exactly the launch of the
- * kernel that does the ACE contraction).  ap_profile(ctx, 1) clears the totals and starts recording,
+ * the kernels of a phase (AP_PHASE_ACE brackets exactly the launches of the
+ * kernels that do the ACE contraction; the FP64 path times each batch of ACE
+ * atoms).  ap_profile(ctx, 1) clears the totals and starts recording,
  * ap_profile(ctx, 0) stops.  ap_profile_read synchronises the device and
  * returns, for the first n phases, the accumulated milliseconds (ms[n]) and
  * the number of timed launches (calls[n]); either pointer may be NULL. */
@@ -415,7 +416,7 @@ enum {
   AP_PHASE_INDENTER = 5,
   AP_PHASE_INTEGRATE = 6,
   AP_PHASE_REDUCE = 7,
-  AP_PHASE_ACE_BOND = 8, /* mixed path: bond basis and bond-gradient kernels */
+  AP_PHASE_ACE_BOND = 8, /* bond basis and bond-gradient kernels */
   AP_N_PHASES = 9
 };
 ap_status ap_profile(ap_ctx* ctx, int32_t enable);

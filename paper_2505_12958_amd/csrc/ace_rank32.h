@@ -26,9 +26,11 @@
 // What bounds it: vector instruction issue (coupling and adjoint of L = 4 take
 // 31k of 70k cycles per tile and keep the vector units busy), then the
 // contraction, then barriers and LDS latency between the short phases.  More
-// wavefronts hide those: 12 per workgroup (168 VGPRs, no spills) at L = 2..6,
-// two workgroups of 8 (128 VGPRs) at L = 0, 1, 7, 8, three of 4 for models
-// with few channels.  The previous layout (8 wavefronts of 256 VGPRs, dense
+// wavefronts hide those: 12 per workgroup (168 VGPRs; L = 4 spills 6) at
+// L = 2..6, two workgroups of 8 (128 VGPRs; 26, 22 and 17 spill at L = 1, 7 and
+// 8) at the others, and for models with few channels workgroups of 4, three to
+// a CU (168 VGPRs; 5 and 30 spill at L = 2 and 3), four at L = 0 (128; 31).
+// The previous layout (8 wavefronts of 256 VGPRs, dense
 // coefficient tiles, X built per set, targets' components split over
 // wavefronts) took 2.18 ms for 20,000 atoms of the (8, 4, nu <= 4) model, this
 // one 1.51 ms; 389,694 atoms of (6, 3, nu <= 3): 7.23 ms, now 3.39 ms.  Also
@@ -345,7 +347,7 @@ __device__ __forceinline__ void rank32_tile(const Rank32Dev& m, const Rank32L& P
       }
     }
   }
-__syncthreads();  // X is dead from here on
+  __syncthreads();  // X is dead from here on
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     float* om = om_buf + (int64_t)p * n_all * nA + (int64_t)tile * kMT32 * nA;

@@ -328,7 +328,6 @@ static ap_status fold_rank64(Ctx* ctx, const ChanMap& chan, const std::vector<Co
   std::vector<int4> mem, units, jobs;
   std::vector<int32_t> rowtab((size_t)(a.L_max + 1) * nidx * nidx, -1), kidx, job_ptr;
   std::vector<double> coef;
-  std::vector<std::vector<std::vector<int>>> steps(a.L_max + 1);  // [L][unit]: its 4-column steps
   for (int L = 0; L <= a.L_max; ++L) {
     Rank64L& P = ctx->r64_lv[L];
     P = Rank64L{};
@@ -1374,9 +1373,8 @@ ap_status ap_ace_forces(ap_ctx* c, const ap_systems* sys, const double* pos, con
                     (int32_t*)ctx->nbr_ace.p, halo, stamp, vir_acc};
   if (ctx->precision == AP_PREC_FP64 && ctx->rank64) {
     const int nA = ctx->ace.nA;
-    // the list's length is on the device, so the buffers are sized for every
-    // atom, but at most kRank64Items at a time (1.3 GB for nA = 200): the
-    // three phases run batch after batch
+    // the buffers are sized for every atom, but at most kRank64Items at a
+    // time: the three phases run batch after batch
     const int n_buf = (int)std::min<int64_t>(std::max<int64_t>(N, 1), kRank64Items);
     if ((st = ensure(ctx, ctx->mix_A, 8 * (size_t)n_buf * nA)) ||
         (st = ensure(ctx, ctx->mix_om, 16 * (size_t)n_buf * nA)) ||

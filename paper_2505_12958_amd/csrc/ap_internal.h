@@ -27,8 +27,6 @@ constexpr int kReduceChunk = 4096;         // atoms per deterministic partial su
     if (e_ != hipSuccess) return fail_hip(ctx, e_, #call, __FILE__, __LINE__); \
   } while (0)
 
-// --------------------------------------------------------------------------
-// device view of the systems of one call
 // Workgroups go to the eight XCDs in turn; this numbers them so that each XCD
 // gets one contiguous run of the work items, whose neighbours then share its L2.
 constexpr unsigned kXcds = 8;
@@ -46,6 +44,8 @@ __host__ __device__ inline unsigned xcd_runs(unsigned b, unsigned n, unsigned ru
   return g0 + r % kXcds * run + r / kXcds;
 }
 
+// --------------------------------------------------------------------------
+// device view of the systems of one call
 struct SysView {
   int32_t n_sys;
   int32_t n_atoms;
@@ -138,17 +138,24 @@ struct MixDev {
 // ---- FP64 rank kernels (k_ace_rank64.hip): C_L as 16 x 4 tiles for the FP64
 // MFMA, empty tiles left out
 constexpr int kT64 = 4;              // atoms per tile
-constexpr int kRank64Items = 262144; // ACE atoms whose A and adjoint are held at once
+// ACE atoms whose A and adjoint are held at once.  The list's length is on the
+// device, so the buffers are sized by the atoms (4.8 KB each at nA = 200, 1.3 GB
+// at most) and batches beyond the list are launched empty, about 20 us each.
+// Smaller batches trade the one for the other: 250,000 atoms, 20,000 listed,
+// 1.78, 1.21 and 0.89 GB of scratch in all at 262,144, 131,072 and 65,536 items,
+// 7.62, 7.64 and 7.68 ms; 2.66 million, 35,229 listed, 6.7, 6.0 and 5.7 GB, 16.1,
+// 16.4 and 16.8 ms.
+constexpr int kRank64Items = 262144;
 constexpr int kRank64MaxN = 8;       // lanes per atom of the adjoint: n_max <= 8
 // doubles of the adjoint's partner sum a lane holds at once (two VGPRs each)
 constexpr int kRank64Lim = 27;
 // units (16 rows of one set) per wavefront and rank: what the complete basis of
 // n_max 8, l_max 4, nu 4 needs
 constexpr int kRank64U[2 * kMaxL + 1] = {3, 5, 6, 6, 5, 3, 3, 1, 1};
-// L <= 1 with at most 3 units per wavefront runs in 128 VGPRs without spills, so
-// two workgroups share a CU (20,518 atoms of the (6, 3, nu <= 3) model: L = 0
-// 122 -> 85 us, L = 1 190 -> 124 us); at L >= 2 the budget spills (L = 2 284 ->
-// 290 us, L = 3 292 -> 308 us)
+// L <= 1 with at most 3 units per wavefront runs in 128 VGPRs (L = 1 spills 48),
+// so two workgroups share a CU (20,518 atoms of the (6, 3, nu <= 3) model: L = 0
+// 122 -> 85 us, L = 1 190 -> 124 us); at L >= 2 the spills cost more than that
+// gives (L = 2 284 -> 290 us, L = 3 292 -> 308 us)
 constexpr int kRank64USmall = 3, kRank64LSmall = 1;
 // parts the M of rank L are cut into for a partner of rank lp (at most 4)
 __host__ __device__ constexpr int rank64_chunks(int lp, int L) {
@@ -285,7 +292,7 @@ struct Ctx {
   Buffer wfp, eF, vir_atom, e_tmp;
   Buffer ace_row, pair_g, ace_counter, ace_rows_list, ace_halo, nbr_ace;
   int32_t halo_stamp = 0;           // last stamp written into ace_halo (0: cleared)
-  Buffer mix_A, mix_om, mix_phi;        // mixed path: A, adjoint (2 sets), phi per ACE atom
+  Buffer mix_A, mix_om, mix_phi;        // rank kernels of both paths: A, adjoint (2 sets), phi per ACE atom
   Buffer mix_bn;                        // mixed path: largest |A_(n,l)|^2 per ACE atom (X scale)
   Buffer partials, flags;               // flags: [0] nbr overflow max count, [1] nonfinite
   Buffer ind_atom;

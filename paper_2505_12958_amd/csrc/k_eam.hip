@@ -212,11 +212,14 @@ __global__ __launch_bounds__(256) void k_eam_density(SysView sv, TableDev rho_t,
   eF[i] = Fv;
 }
 
-// Waits on the list entries and the gathered records.  The entries of four bonds
-// are loaded together, so their way from HBM is paid once for the four (us,
-// against a bond at a time with five wavefronts a SIMD: 1.27 million atoms closed
-// form 620 -> 589, 2.66 million 1265 -> 1157, 250,000 102 -> 98; five wavefronts
-// spill here: 600, 1265, 103; batches of eight 606, 2120, 179).
+// Waits on the list entries and the gathered records, four wavefronts a SIMD; with
+// tables also on LDS (a lookup's 16-byte reads start in half of the banks: 250,000
+// atoms, 74 % of the LDS cycles are conflicts, 68 % in the density pass).  The
+// entries of four bonds are loaded together, so their way from HBM is paid once
+// for the four (us, against a bond at a time with five wavefronts a SIMD: 1.27
+// million atoms closed form 620 -> 589, 2.66 million 1265 -> 1157, 250,000
+// 102 -> 98; five wavefronts spill here: 600, 1265, 103; batches of eight 606,
+// 2120, 179).
 template <bool kOrtho, bool kLds, bool kAn, int LN>
 __global__ __launch_bounds__(256, 4) void k_eam_force(SysView sv, TableDev rho_t, TableDev phi_t,
                                                    EamAnalyticDev an,
@@ -321,15 +324,16 @@ __global__ __launch_bounds__(256, 4) void k_eam_force(SysView sv, TableDev rho_t
 }
 
 // Threads per atom.  An atom's 58 or so bonds are one chain of gathers, square
-// roots and divisions: while the chip is not full, splitting it sets the time
-// (us, density + force pass, against one thread per atom: tables, 2,000 atoms
-// 31 + 42 -> 6.8 + 8.8 with 16 threads; 31,250 atoms 32 + 47 -> 13.3 + 20.2 with
-// 4, 12.6 + 25.1 with 16; 108,000 atoms 36 + 71 -> 25.2 + 51.7 with 4, 31 + 79
-// with 16).  A full chip is bound by the gathered 32-byte records, and the
-// split only shortens each block's chain: 250,000 atoms 54.8 + 114.6 with one
-// thread, 52.9 + 109.7 with 2, 54.4 + 117 with 4; 2.66 million 631 + 1516,
-// 641 + 1406, 680 + 1387.  Closed form, 1.27 million atoms: 421 + 699, 354 + 683,
-// 336 + 699 (418 + 958 when the knots were added up one by one).
+// roots and divisions: while the chip is not full, splitting it sets the time.
+// On a full chip the split only shortens each block's chain.  us, density +
+// force pass with 1, 2, 4 and 16 threads, tables:
+//      2,000 atoms   23 +   44,  15 +   23,   9 +   15,   5 +    8
+//     31,250 atoms   24 +   45,  16 +   25,  12 +   18,  13 +   21
+//    108,000 atoms   35 +   62,  28 +   50,  25 +   47,  31 +   65
+//    250,000 atoms   55 +  106,  54 +  102,  54 +  103,  68 +  144
+//  2,660,283 atoms  568 + 1219, 610 + 1123, 647 + 1108, 746 + 1714
+// closed form (418 + 958 with one thread when the knots were added up one by one):
+//  1,272,112 atoms  297 +  577, 278 +  559, 260 +  577, 322 +  858
 constexpr int kEamSplit16 = 8192, kEamSplit4 = 131072;
 
 hipError_t launch_eam(const Ctx& c, const SysView& sv, const double4* pos4, const int32_t* nbr,

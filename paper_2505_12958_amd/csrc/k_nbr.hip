@@ -300,7 +300,8 @@ __global__ __launch_bounds__(256) void k_fill_nbr_big(SysView sv, const double* 
 // in one L2.  us, before -> after: 250,000 atoms 202 -> 134, 1.27 million
 // 1032 -> 627, 2.66 million 2284 -> 1282, 96 sheared cells of 250 to 16,000 atoms
 // (the FP64 test of every candidate fell away) 620 -> 201.  Seven workgroups a
-// CU rather than six: 1282 against 1336 us at 2.66 million; eight spill.
+// CU (2 VGPRs spill) rather than six: 1282 against 1336 us at 2.66 million; with
+// eight more spill, 670 against 622 us at 1.27 million.
 constexpr int kCellThreads = 256;
 constexpr int kCellWaves = kCellThreads / 64;
 constexpr int kMaxCand = 512;
